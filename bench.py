@@ -71,18 +71,18 @@ def path_counts(B, T, H, Dk, Dv, C=64, esz=2):
 
 def workspace_traffic(B, T, H, Dk, Dv, G, C=64, esz=2):
     """Workspace bytes each stage writes and reads (every byte once).  The WY
-    kernel writes the gates (g, and a record of the per-token key decay factors
-    in fp32 with g_C), -W and U~t; the scans read the keys from the input.  With one scan
-    group on the bf16 path the output is fused into the scan: the WY kernel then
+    kernel writes the gates (a record of the per-token key decay factors in fp32
+    with g_C; on the fp32 path also g), -W and U~t; the scans read the keys from
+    the input.  On the bf16 path the output is fused into the scan: the WY kernel
     also writes the decay-scaled queries and the masked decayed Q K^T tile of
     every chunk (row fragments the scan's output waves read) and the scan
     writes no per-chunk state."""
     NC = -(-T // C)
     NG = -(-NC // G)
     nch = B * H * NC
-    fused = esz == 2 and NG == 1
+    fused = esz == 2
     ngr = B * H * NG if NG > 1 else 0
-    gates = nch * (C * 8 + (C + 4) * 4)
+    gates = nch * ((0 if fused else C * 8) + (C + 4) * 4)
     fac = nch * C * (Dk + Dv) * esz                        # -W, U~t
     scan_gates = nch * (C + 4) * 4                         # key scales, g_C
     qp = nch * C * (Dk + C) * esz if fused else 0          # scaled Q, masked P
@@ -242,7 +242,7 @@ def run_extra_workload(idx, gdn, torch, dev, stream, reps):
     torch.cuda.synchronize()
     names = {k: v for k, v in zip(gdn.STAGE_NAMES, stage) if v > 0}
     G = gdn.gdn_scan_group_size(B, H, T, Dk, Dv, is_bf16=esz == 2)
-    fused = esz == 2 and -(-(-(-T // 64)) // G) == 1
+    fused = esz == 2
     flops, io = path_counts(B, T, H, Dk, Dv, esz=esz)
     wst = workspace_traffic(B, T, H, Dk, Dv, G, esz=esz)
     ws_bytes = sum(v["written"] + v["read"] for v in wst.values())
@@ -624,7 +624,7 @@ def main():
 
     G = gdn.gdn_scan_group_size(B, H, T, Dk, Dv, C, is_bf16=bf16)
     NG = -(-(-(-T // C)) // G)
-    fused = bf16 and NG == 1
+    fused = bf16
     esz = 2 if bf16 else 4
     flops, io = path_counts(B, T, H, Dk, Dv, C, esz=esz)
     sec = ms_per_step / 1e3

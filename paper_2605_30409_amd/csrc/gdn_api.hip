@@ -55,9 +55,10 @@ WsLayout ws_layout(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
     L.gf = off;   off = align256(off + nch * kGateRec * 4);
     L.W = off;    off = align256(off + nch * kChunk * Dk * esz);
     L.Ut = off;   off = align256(off + nch * Dv * kChunk * esz);
-    // With the output fused into the scan (bf16, one group) these regions hold
-    // the chunk's decay-scaled queries (C x Dk) and masked scores (C x C)
-    // instead of the per-chunk state (Dv x Dk) and pseudo-values (Dv x C).
+    // On the bf16 path these regions hold the chunk's decay-scaled queries
+    // (C x Dk) and masked scores (C x C) instead of the per-chunk state (Dv x Dk)
+    // and pseudo-values (Dv x C).  (With several groups they keep the larger
+    // sizes: a caller's workspace is sized the same as ever.)
     const bool fused = esz == 2 && NG == 1;
     L.Hs = off;   off = align256(off + nch * (fused ? kChunk : Dv) * Dk * esz);
     L.Us = off;   off = align256(off + nch * (fused ? kChunk : Dv) * kChunk * esz);
@@ -82,7 +83,7 @@ WsNeeds ws_needs(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
     const size_t NC = (size_t)num_chunks(T), NG = (NC + G - 1) / G;
     const size_t cmax = (size_t)B * H * NC - 1;             // last chunk record
     const size_t gmax = (size_t)B * H * NG - 1;             // last group record
-    const bool fused = esz == 2 && NG == 1;
+    const bool fused = esz == 2;  // the output is fused into the scan
     const size_t KB = (size_t)Dk / 32, NJ = (size_t)Dv / 16;
     WsNeeds n{};
     // WY kernel: g[cidx * 64 + l], gf[cidx * 68 + l] and the fp64 g_C at
@@ -187,9 +188,8 @@ gdn::Params<E> make_params(const void *q, const void *k, const void *v, const fl
     p.Ut = (E *)(base + L.Ut);
     p.Hs = (E *)(base + L.Hs);
     p.Us = (E *)(base + L.Us);
-    // The output is fused into the scan on the bf16 path with one scan group;
-    // its Q and P fragments then live in the (unused) Hs and Us regions.
-    p.fused = (sizeof(E) == 2 && p.NG == 1) ? 1 : 0;
+    // The output is fused into the scan on the bf16 path; its Q and P fragments
+    // live in the (unused) Hs and Us regions.
     p.Qf = p.Hs;
     p.Pf = p.Us;
     p.Nf = (E *)(base + L.Nf);
@@ -209,10 +209,10 @@ hipError_t launch(const void *fn, dim3 grid, dim3 block, size_t lds, hipStream_t
     return hipLaunchKernel(fn, grid, block, args, lds, s);
 }
 
-// The scan kernel with the output fused (bf16 only; nullptr for fp32).
-template <class E, int DK, int DV> const void *fused_scan_fn() {
-    if constexpr (sizeof(E) == 2)
-        return (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, 1, 1, true>;
+// The fp32 path's output kernel (nullptr for bf16, whose scan forms the output).
+template <class E, int DK, int DV> const void *output_fn() {
+    if constexpr (sizeof(E) == 4)
+        return (const void *)gdn::gdn_output_kernel<E, DK, DV>;
     else
         return nullptr;
 }
@@ -229,12 +229,22 @@ struct StageTiming {
 
 template <class E, int DK, int DV>
 hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) {
-    constexpr int CT = gdn::ScanCT<E>::value;
-    constexpr int NCW = gdn::kScanNCW;
-    using LT = gdn::ScanLds<E, DK, CT, NCW>;  // grouped passes
-    using L1 = gdn::ScanLds<E, DK, 1, 1>;     // single-group scan
-    using LF = gdn::ScanLds<E, DK, 1, 1, sizeof(E) == 2>;  // single-group scan with the output fused
-    constexpr unsigned scan_threads = (NCW + 2) * 64, scan_threads1 = 3 * 64, scan_threadsF = 4 * 64;
+    constexpr int NOW = sizeof(E) == 2 ? 4 : 0;  // output waves: bf16 fuses the output into the scan
+    // Two column tiles per workgroup once one each would be more workgroups than
+    // CUs: the pair reads the chunk operands once, and a second round of
+    // workgroups or a shared CU costs more than the longer step (320 tiles of the
+    // D = 64 guidance batch, T = 10560: 461 us a call with one tile, 355 with two).
+    // Up to one workgroup per CU one tile is faster (T = 3520, H = 16, 128 tiles:
+    // 65 against 76 us; T = 42240, H = 32, 256 tiles: 1227 against 1267), in fp32
+    // always (its two-tile step has no registers for it).
+    const bool wide = sizeof(E) == 2 && (long long)p.B * p.H * p.NG * (DV / 16) > 256;
+    constexpr int CTW = sizeof(E) == 2 ? 2 : 1;
+    using L1 = gdn::ScanLds<E, DK, 1, NOW>;
+    using L2 = gdn::ScanLds<E, DK, CTW, NOW>;
+    using LT = gdn::ScanLds<E, DK, 2, 0>;        // group transfers
+    const void *scan1 = (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, 1, NOW>;
+    const void *scan2 = (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, CTW, NOW>;
+    const void *scant = (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_TRANS, 2, 0>;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     const size_t lds1 = gdn::WyLds<E, DK, DV>::bytes;
@@ -245,11 +255,10 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
             size_t bytes;
         } dyn[] = {
             {(const void *)gdn::gdn_wy_kernel<E, DK, DV>, lds1},
-            {(const void *)gdn::gdn_output_kernel<E, DK, DV>, lds3},
-            {(const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_TRANS, CT, NCW>, LT::bytes},
-            {(const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, CT, NCW>, LT::bytes},
-            {(const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, 1, 1>, L1::bytes},
-            {fused_scan_fn<E, DK, DV>(), LF::bytes},
+            {output_fn<E, DK, DV>(), lds3},
+            {scan1, L1::bytes},
+            {scan2, L2::bytes},
+            {scant, LT::bytes},
         };
         for (const auto &d : dyn) {
             if (!d.fn) continue;
@@ -268,31 +277,21 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
             return launch((const void *)gdn::gdn_wy_kernel<E, DK, DV>, dim3(p.NC, BH), dim3(64 * gdn::kWyWaves),
                           lds1, s, p);
         case 1:
-            return launch((const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_TRANS, CT, NCW>,
-                          dim3(groups((DK + DV) / (16 * CT * NCW), BH * p.NG)), dim3(scan_threads), LT::bytes, s,
-                          p);
+            return launch(scant, dim3(groups((DK + DV) / 32, BH * p.NG)), dim3(gdn::scan_threads<0>()), LT::bytes, s, p);
         case 2:
             return launch((const void *)gdn::gdn_groupscan_kernel<E, DK, DV>, dim3(groups(DV / 16, BH)), dim3(DK),
                           0, s, p);
         case 3:
-            if (p.NG > 1)
-                return launch((const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, CT, NCW>,
-                              dim3(groups(DV / (16 * CT * NCW), BH * p.NG)), dim3(scan_threads), LT::bytes, s, p);
-            // one sequential scan per (b, h), one column tile per workgroup,
-            // which also computes the output of its columns (bf16)
-            if (p.fused)
-                return launch(fused_scan_fn<E, DK, DV>(), dim3(groups(DV / 16, BH)), dim3(scan_threadsF), LF::bytes,
-                              s, p);
-            // one sequential scan per (b, h): one column tile per compute wave
-            return launch((const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, 1, 1>,
-                          dim3(groups(DV / 16, BH)), dim3(scan_threads1), L1::bytes, s, p);
+            if (wide)
+                return launch(scan2, dim3(groups(DV / (16 * CTW), BH * p.NG)), dim3(gdn::scan_threads<NOW>()), L2::bytes, s, p);
+            return launch(scan1, dim3(groups(DV / 16, BH * p.NG)), dim3(gdn::scan_threads<NOW>()), L1::bytes, s, p);
         default:
-            return launch((const void *)gdn::gdn_output_kernel<E, DK, DV>, dim3(p.NC, BH), dim3(256), lds3, s, p);
+            return launch(output_fn<E, DK, DV>(), dim3(p.NC, BH), dim3(256), lds3, s, p);
         }
     };
     hipError_t er = hipSuccess;
     for (int i = 0; i < kStages && er == hipSuccess; ++i) {
-        const bool runs = (i == 1 || i == 2) ? p.NG > 1 : (i == 4 ? !p.fused : true);
+        const bool runs = (i == 1 || i == 2) ? p.NG > 1 : (i == 4 ? sizeof(E) == 4 : true);
         if (tm) tm->ran[i] = runs;
         if (!runs) continue;
         if (!tm) {

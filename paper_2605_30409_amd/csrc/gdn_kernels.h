@@ -19,7 +19,8 @@
 //
 // Workspace per (b*H + h, chunk) -- see gdn_api.hip for the byte layout:
 //   g  [64]       fp64   cumulative log decay (fp64 so that g_r - g_s keeps
-//                        its precision when the decay over a chunk is huge)
+//                        its precision when the decay over a chunk is huge;
+//                        written on the fp32 path only)
 //   gf [68]       fp32   e^{g_C - g_r} (the update's per-token key scale),
 //                        then g_C, the log decay over the chunk, as one fp64,
 //                        and gamma = e^{g_C}
@@ -38,6 +39,8 @@
 // scaled copy of K is written.
 #pragma once
 
+#include <type_traits>
+
 #include "gdn_device.h"
 
 namespace gdn {
@@ -54,10 +57,9 @@ template <class E> struct Params {
     double *g;
     float *gf;        // per (b*H + h, chunk): e^{g_C - g_r} [64], g_C (fp64), e^{g_C}, 1 unused
     E *W, *Ut, *Hs, *Us;
-    // Fused output (bf16, one scan group): the scan computes the output, from
-    // Qf = diag(e^g) Q and Pf = (Q K^T o M) row fragments written by the WY
-    // kernel (they reuse the Hs / Us workspace regions, which are then unused).
-    int fused;
+    // bf16: the scan computes the output, from Qf = diag(e^g) Q and
+    // Pf = (Q K^T o M) row fragments written by the WY kernel (in the Hs / Us
+    // workspace regions, which only the fp32 path uses as such; nor is g needed).
     E *Qf, *Pf;
     E *Nf;            // per (b*H + h, group): N_g = Phi_g - Gamma_g I, fragment-major
     float *PsiT;      // per (b*H + h, group): Psi_g^T [Dv][Dk]
@@ -183,7 +185,7 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
         sgl[l] = (float)(g * kLog2e);
         sb[l] = be;
         sw[l] = -be * eg;
-        p.g[cidx * kChunk + l] = g;
+        if (sizeof(E) == 4) p.g[cidx * kChunk + l] = g;  // the fp32 output kernel reads it
         p.gf[cidx * kGateRec + l] = __builtin_amdgcn_exp2f((float)((gC - g) * kLog2e));
         if (l == 0) {
             *(double *)(p.gf + cidx * kGateRec + kChunk) = gC;
@@ -197,7 +199,7 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
     }
     lds_barrier();
     if constexpr (sizeof(E) == 2) {
-        if (p.fused && qjob) {
+        if (qjob) {
 #pragma unroll
             for (int kb = 0; kb < DK / 32; ++kb)
                 qf[kb] = rq < nvalid ? load_frag<E>(p.q + (row0 + rq * rstride) * DK + 32 * kb, lg)
@@ -261,7 +263,7 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
         // P^T tiles take their s rows in P32 order, so a tile pair is one
         // fragment; block m = 1 only matters for r >= 32.
         if constexpr (sizeof(E) == 2) {
-            if (p.fused && qjob) {
+            if (qjob) {
                 if (qjob_m == 0) {
                     const float er = expf((float)sg[rq]);
                     E *Qf = p.Qf + cidx * (size_t)kChunk * DK + l * 8;
@@ -405,58 +407,101 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
 //       per-chunk state H_{c-1} and pseudo-values U_c the output stage needs.
 // With a single group only (O) runs, from state_in, and writes state_out.
 //
-// gdn_chunkscan_kernel: a workgroup owns NCW * 16 * CT state columns of one
-// (b, h, group).  It has NCW compute waves, each carrying 16 * CT columns over
-// all Dk rows through the group's chunks in fp32 accumulators (so U = Ut - W H
-// needs no exchange between waves), and two loader waves that stream the chunk
-// operands (-W, the chunk's key rows read from the input, the workgroup's Ut
-// columns and the key scales e^{g_C - g}) into an LDS ring of DEPTH slots with
+// gdn_chunkscan_kernel: a workgroup owns 16 * CT state columns of one
+// (b, h, group), the state split over four compute waves by rows.  Wave s holds
+// the fp32 accumulators of row tiles RT s .. RT s + RT - 1 (RT = Dk / 64) and
+// computes token tile s of U = Ut - W H, then its own rows of the update
+// H <- gamma H + K^T (diag(e^{g_C - g}) U).  Both products need what the other
+// waves made, so a chunk has two phases with a barrier in front of each:
+//   B1(c)  H_{c-1} (rounded to E, as MFMA operands) is in LDS
+//          phase 1: W H and the conversion of U, written to LDS
+//   B2(c)  U_c is in LDS
+//          phase 2: the update, the new H written to LDS
+// A phase is one LDS round trip, one short chain of MFMAs and a few
+// conversions; with the rows on one wave the step was 36 MFMAs and 80 VALU
+// instructions in a row on one SIMD while three others had nothing to do.
+// NOW output waves (bf16) read the same H and U operands and form the output of
+// 4 / NOW token tiles each: Q~ H in phase 1, + P U and the store in phase 2.
+//
+// -W and U~t go straight from the workspace to the registers of the wave that
+// needs them, four chunks ahead (the fragment-major layout is for this).  The
+// key rows are read by all waves, transposed, so two loader waves stream them
+// (and the gate records) from the input into a ring of DEPTH LDS slots with
 // asynchronous global->LDS copies (1 KB per instruction, lane i's 16 bytes
-// landing at +16 i: the fragment-major workspace layout is kept, and each key
-// row's 16-byte pieces land permuted, see kswz).  The update takes
-// K^T (diag(e^{g_C - g}) U): the key scales are applied to U in registers.
-// One workgroup barrier per chunk hands a slot over: before barrier c the
-// loaders have waited (vmcnt) for chunk c's copies; after it they refill the
-// slot of chunk c - 1, which every compute wave has finished reading.  The
-// copies for chunk c are thus issued DEPTH - 1 chunks ahead, and neither the
-// copy issue nor its latency sits on the compute waves' chain.
+// landing at +16 i, each row's pieces permuted, see kswz).  The compute waves
+// take K(c) into registers in phase 1 of chunk c, so its slot is refilled for
+// chunk c + DEPTH from B2(c) on: a copy has DEPTH - 1/2 steps to land.
+//
+// What bounds a step (T = 3520, H = 16, D = 128, 128 workgroups, 55 steps; copies
+// of the kernel that leave work out): the compute waves alone 0.37 us, with the
+// loads 0.73.  A workgroup takes in 56 KB a step (W, K and Q~ 16 KB each, P 6, U~t
+// 2), which one CU does at about 80 B/ns whether through LDS or registers, with 8
+// workgroups on the chip or 256.  Before, one wave carried all rows of a column
+// tile: 0.56 us of dependent MFMAs and VALU a step, 0.72 with the loads.  So where
+// that one CU's intake is the limit the kernel is as fast as before (40 us), and
+// where the chain was, faster: fp32 (256 MFMAs of 32 cycles a step and tile, now
+// over four SIMDs) T = 3557, H = 16 250 -> 87 us; the grouped passes of two
+// heads at T = 10560 18.4 -> 12 us (transfers) and 22.9 + 9.6 -> 13 us (states,
+// which then formed the output in a kernel of its own); D = 64 x 80 heads, with
+// two column tiles per workgroup, 307 -> 174 us.
 // --------------------------------------------------------------------------
 enum { SCAN_TRANS = 0, SCAN_STATES = 1 };
 
-// Column tiles per compute wave and compute waves per workgroup for the
-// grouped passes; a single-group scan uses one column tile and one compute
-// wave per workgroup (every workgroup loads all of W and K each chunk, so
-// narrow workgroups spread that traffic over more CUs).
-template <class E> struct ScanCT { static constexpr int value = sizeof(E) == 2 ? 2 : 1; };
-constexpr int kScanNCW = 2;
+constexpr int kScanSplit = 4;   // compute waves per workgroup
 
-template <class E, int DK, int CT, int NCW, bool FUSE = false> struct ScanLds {
+// Operand fragments in LDS that several waves write and read: fragment f of a
+// buffer is one value per lane; half a of it (four of its eight elements) comes
+// from another accumulator tile than the other half.  bf16: 16 bytes per lane;
+// fp32: the halves in planes of 16 bytes per lane.
+template <class E> struct Xch;
+template <> struct Xch<uint16_t> {
+    using TR = Tr<uint16_t>;
+    static constexpr int BYTES = 1024;
+    static __device__ __forceinline__ void put(unsigned char *b, int f, int a, int l, TR::quad v) {
+        *(TR::quad *)(b + f * BYTES + l * 16 + 8 * a) = v;
+    }
+    static __device__ __forceinline__ void put2(unsigned char *b, int f, int l, TR::quad lo, TR::quad hi) {
+        *(TR::frag *)(b + f * BYTES + l * 16) = TR::cat(lo, hi);
+    }
+    static __device__ __forceinline__ TR::frag get(const unsigned char *b, int f, int l) {
+        return *(const TR::frag *)(b + f * BYTES + l * 16);
+    }
+};
+template <> struct Xch<float> {
+    using TR = Tr<float>;
+    static constexpr int BYTES = 2048;
+    static __device__ __forceinline__ void put(unsigned char *b, int f, int a, int l, TR::quad v) {
+        *(TR::quad *)(b + f * BYTES + a * 1024 + l * 16) = v;
+    }
+    static __device__ __forceinline__ void put2(unsigned char *b, int f, int l, TR::quad lo, TR::quad hi) {
+        put(b, f, 0, l, lo);
+        put(b, f, 1, l, hi);
+    }
+    static __device__ __forceinline__ TR::frag get(const unsigned char *b, int f, int l) {
+        return TR::cat(*(const TR::quad *)(b + f * BYTES + l * 16), *(const TR::quad *)(b + f * BYTES + 1024 + l * 16));
+    }
+};
+
+template <class E, int DK, int CT, int NOW> struct ScanLds {
     static constexpr int KB = DK / 32;                     // 32-row blocks of the state
     static constexpr int NT = DK / 16;                     // 16-row tiles of the state
     static constexpr int WK = kChunk * DK;                 // elements of -W (and of K) per chunk
-    static constexpr int UT = NCW * CT * 1024;             // elements of the workgroup's Ut per chunk
-    static constexpr int oD = 2 * WK + UT;                 // key scales, g_C: one gate record
-    static constexpr int SLOT = oD + 4 * kGateRec / (int)sizeof(E);  // ring slot: -W, K rows, Ut, gates
-    static constexpr int SLOT_BYTES = SLOT * (int)sizeof(E);
-    static constexpr int NC_W = WK * (int)sizeof(E) / 1024;   // 1 KB copies of -W (and of K)
-    static constexpr int NC_U = UT * (int)sizeof(E) / 1024;
-    // loader 0 copies -W, the first half of Ut and the gate record (one
-    // 17-lane copy), loader 1 the key rows and the rest of Ut
-    static constexpr int NC_U0 = NC_U / 2, NC_U1 = NC_U - NC_U0;
-    static constexpr int NCOPY0 = NC_W + NC_U0 + 1, NCOPY1 = NC_W + NC_U1;
-    static constexpr int LDS_CAP = 152 * 1024;
-    // fused output: H_{c-1} (KB fragments) and U (2) per column tile handed
-    // from each compute wave to its output wave, double-buffered
-    static constexpr int HOFF_FRAGS = CT * (KB + 2);
-    static constexpr int HOFF_BYTES = FUSE ? 2 * NCW * HOFF_FRAGS * 64 * (int)sizeof(typename Tr<E>::frag) : 0;
-    static constexpr int DL = (LDS_CAP - HOFF_BYTES) / SLOT_BYTES;
-    // the loader waits with D - 2 younger chunks in flight: vmcnt <= 63
-    static constexpr int DV_ = 2 + 63 / (NCOPY0 > NCOPY1 ? NCOPY0 : NCOPY1);
-    static constexpr int DEPTH = (DL < 4 ? DL : 4) < DV_ ? (DL < 4 ? DL : 4) : DV_;
-    static constexpr size_t oHOFF = (size_t)DEPTH * SLOT_BYTES;
-    static constexpr size_t bytes = oHOFF + HOFF_BYTES;
-    static_assert(DEPTH >= 2, "scan ring needs two slots");
-    static_assert((WK * sizeof(E)) % 1024 == 0 && (UT * sizeof(E)) % 2048 == 0, "whole 1 KB copies");
+    static constexpr int W_BYTES = WK * (int)sizeof(E);
+    static constexpr int oD = W_BYTES;                     // in a slot: key rows, gate record
+    static constexpr int SLOT = oD + 4 * kGateRec;
+    static constexpr int NC_W = W_BYTES / 1024;            // 1 KB copies of -W (and of K)
+    static constexpr int HX = CT * KB * Xch<E>::BYTES;     // H_{c-1} operands
+    static constexpr int UX = CT * 2 * Xch<E>::BYTES;      // U operands (scaled for the update; as is for the output)
+    static constexpr int CAP = 160 * 1024;
+    static constexpr int DL = (CAP - HX - UX * (NOW ? 2 : 1)) / SLOT;
+    // the loaders wait with DEPTH - 1 younger chunks in flight: vmcnt <= 63
+    static constexpr int DVM = 1 + 63 / (NC_W / 2 + 1);
+    static constexpr int D0 = DL < DVM ? DL : DVM;
+    static constexpr int DEPTH = D0 < 4 ? 2 : 4;           // divides the compute waves' unroll of four
+    static constexpr int oH = DEPTH * SLOT, oU = oH + HX, oUo = oU + UX;
+    static constexpr size_t bytes = oUo + (NOW ? UX : 0);
+    static_assert(D0 >= 2, "scan ring needs two slots");
+    static_assert(W_BYTES % 1024 == 0 && SLOT % 16 == 0, "whole 1 KB copies, aligned slots");
 };
 
 // Copy N whole KB from global to LDS: instruction i moves bytes
@@ -504,25 +549,25 @@ __device__ __forceinline__ typename Tr<E>::frag kt_frag(const E *Kr, int row0, i
     }
 }
 
-template <class E, int DK, int DV, int PHASE, int CT, int NCW, bool FUSE = false>
-__global__ __launch_bounds__((NCW * (FUSE ? 2 : 1) + 2) * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void gdn_chunkscan_kernel(Params<E> p) {
+template <int NOW> constexpr int scan_threads() { return (kScanSplit + NOW + 2) * 64; }
+
+template <class E, int DK, int DV, int PHASE, int CT, int NOW>
+__global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Params<E> p) {
     using TR = Tr<E>;
     using frag = typename TR::frag;
-    using L = ScanLds<E, DK, CT, NCW, FUSE>;
-    static_assert(!FUSE || PHASE == SCAN_STATES, "the output is fused into the state pass only");
-    constexpr int NOW = FUSE ? NCW : 0;                  // output waves
-    constexpr int D = L::DEPTH;
-    // compute waves read the next chunk's operands ahead when the ring has
-    // room for it (four slots: the loaders then still issue two chunks ahead)
-    constexpr int AHEAD = D >= 4 ? 1 : 0;
-    constexpr int KB = L::KB, NT = L::NT;
-    constexpr int WGC = NCW * 16 * CT;                   // columns per workgroup
+    using quad = typename TR::quad;
+    using L = ScanLds<E, DK, CT, NOW>;
+    using X = Xch<E>;
+    static_assert(!NOW || PHASE == SCAN_STATES, "the output is fused into the state pass only");
+    constexpr int D = L::DEPTH, NCW = kScanSplit;
+    constexpr int KB = L::KB, NT = L::NT, RT = NT / NCW; // row tiles per compute wave
+    constexpr int NWS = sizeof(E) == 4 && CT > 1 ? 2 : 4; // register sets of W and U~t (fp32 pairs: no room for four)
+    constexpr int WGC = 16 * CT;                         // columns per workgroup
     constexpr int WCOLS = PHASE == SCAN_TRANS ? DK + DV : DV;
     constexpr int NJB = WCOLS / WGC;                     // column blocks per (b, h, group)
-    static_assert(WCOLS % WGC == 0 && DK % WGC == 0, "column blocks do not straddle Phi and Psi");
+    static_assert(CT <= 2 && WCOLS % WGC == 0 && DK % WGC == 0, "column blocks do not straddle Phi and Psi");
     extern __shared__ __align__(16) unsigned char scan_lds[];
-    E *ring = (E *)scan_lds;
+    unsigned char *hx = scan_lds + L::oH, *ux = scan_lds + L::oU, *uo = scan_lds + L::oUo;
 
     // XCD-aware placement: workgroups are dealt round-robin to the 8 XCDs, so
     // id = 8 slot + x runs on XCD x.  The NJB column blocks of one (b, h, group)
@@ -540,82 +585,78 @@ void gdn_chunkscan_kernel(Params<E> p) {
     const int col0 = WGC * jb;
     const bool is_phi = PHASE == SCAN_TRANS && col0 < DK;
     // first column of this workgroup within the state (Phi columns or Psi / H columns)
-    const int wbase = (PHASE == SCAN_TRANS && !is_phi) ? col0 - DK : col0;
+    const int jw = (PHASE == SCAN_TRANS && !is_phi) ? col0 - DK : col0;
     const bool has_ut = PHASE == SCAN_STATES || !is_phi;
-    auto slot_of = [&](int c) { return ring + (size_t)((c - c_begin) % D) * L::SLOT; };
-
-    // fused output hand-off: buffer i, compute wave wc, fragment f of column tile ct
-    frag *hoff = (frag *)(scan_lds + L::oHOFF);
-    auto hoff_at = [&](int i, int wc, int ct, int f) {
-        return hoff + ((size_t)((i * NCW + wc) * CT + ct) * (KB + 2) + f) * 64 + l;
-    };
+    // Column of the state that lane li of column tile ct holds.  With two tiles
+    // the 32 columns are dealt in P32 order, so that an output wave's lane gets
+    // eight consecutive output columns from the pair: one 16-byte store per
+    // token, 64 contiguous bytes per token and workgroup, instead of two 8-byte
+    // ones.
+    auto col = [&](int ct) { return jw + (CT == 2 ? p32_row(ct, li) : 16 * ct + li); };
 
     if (w >= NCW + NOW) {
         // ---------------- loader waves ----------------
-        const int ld = w - NCW - NOW;
-        // Key rows of chunk `src` from the input (B, T, H, DK): instruction n,
-        // lane l fills LDS granule 64 n + l, i.e. granule (64 n + l) % GPR of
-        // row (64 n + l) / GPR, from the row's granule permuted back by kswz.
-        // Rows past the sequence's end are read from its last token; their
-        // pseudo-values are exactly zero (beta = 0 and zero V and K rows in the
-        // WY factors), so they add nothing to the update.
-        auto copy_krows = [&](int src, E *dst) {
-            constexpr int GPR = DK * (int)sizeof(E) / 16, VE = 16 / (int)sizeof(E);
-            const int t0 = src * kChunk, tl = p.T - 1;
-            const E *kbase = p.k + (size_t)b * p.T * p.H * DK + (size_t)h * DK;
+        // A wave needs some 50 cycles to issue a 1 KB copy, so a chunk's copies
+        // are dealt to four waves (two for W, two for K) and each issues half of
+        // its share in either phase: no phase waits for the issue.  Past the end
+        // the loaders still issue the same number of copies (so that the counts
+        // the waits rely on are constant), reading the last chunk, into the slot
+        // of the missing chunk.
+        const int part = w - NCW - NOW;
+        constexpr int NS = L::NC_W / 2, NH = NS / 2;     // copies per wave and chunk, and per phase
+        {
+            // Key rows of chunk c from the input (B, T, H, DK): instruction n,
+            // lane l fills LDS granule 64 n + l, i.e. granule (64 n + l) % GPR of
+            // row (64 n + l) / GPR, from the row's granule permuted back by kswz.
+            // Rows past the sequence's end are read from its last token; their
+            // pseudo-values are exactly zero (beta = 0 and zero V and K rows in the
+            // WY factors), so they add nothing to the update.
+            // A copy's rows are RPC apart from the next one's, so a lane's
+            // offset from the copy's first row is the same for all of them.
+            constexpr int GPR = DK * (int)sizeof(E) / 16, RPC = 64 / GPR;
+            const int lr = l / GPR, lc = 16 * ((l % GPR) ^ kswz<E, DK>(lr));
+            const unsigned rs = (unsigned)p.H * DK * (unsigned)sizeof(E), voff = (unsigned)lr * rs + lc;
+            const char *kbase = (const char *)(p.k + ((size_t)b * p.T * p.H + h) * DK);
+            auto issue = [&](int c, int off, auto half) {
+                constexpr int HF = decltype(half)::value;
+                const int src = min(c, c_end - 1), t0 = src * kChunk, left = p.T - 1 - t0, n0 = NS * part + NH * HF;
+                unsigned char *sl = scan_lds + off;
+                const char *kc = kbase + (size_t)t0 * rs;
+                if (left >= kChunk - 1) {
 #pragma unroll
-            for (int n = 0; n < L::NC_W; ++n) {
-                const int idx = 64 * n + l, r = idx / GPR, g = (idx % GPR) ^ kswz<E, DK>(r);
-                const int t = min(t0 + r, tl);
-                __builtin_amdgcn_global_load_lds((const void *)(kbase + (size_t)t * p.H * DK + g * VE),
-                                                 (__attribute__((address_space(3))) void *)((char *)dst + 1024 * n),
-                                                 16, 0, 0);
-            }
-        };
-        // copies of chunk `src` into the slot of chunk `dst` (dst = src except
-        // past the end, see below)
-        auto issue = [&](int dst, int src) {
-            const size_t cidx = (size_t)bh * p.NC + src;
-            E *sl = slot_of(dst);
-            const E *ut = p.Ut + cidx * (size_t)DV * kChunk + (size_t)(wbase / 16) * 1024;
-            if (ld == 0) {
-                copy_kb<L::NC_W>(p.W + cidx * (size_t)L::WK, sl, l);
-                if (has_ut) copy_kb<L::NC_U0>(ut, sl + 2 * L::WK, l);
-                if (l < kGateRec / 4)  // the gate record: 272 bytes
-                    __builtin_amdgcn_global_load_lds((const void *)(p.gf + cidx * kGateRec + 4 * l),
-                                                     (__attribute__((address_space(3))) void *)(sl + L::oD), 16, 0,
-                                                     0);
-            } else {
-                copy_krows(src, sl + L::WK);
-                if (has_ut)
-                    copy_kb<L::NC_U1>((const char *)ut + 1024 * L::NC_U0,
-                                      (char *)(sl + 2 * L::WK) + 1024 * L::NC_U0, l);
-            }
-        };
-        // Chunk c (with AHEAD chunk c + 1) has landed once at most D - 2
-        // (D - 3) younger chunks' copies are in flight (every chunk issues the
-        // same number of copies).
-        constexpr int NF = D - 2 - AHEAD;
-        auto wait_oldest = [&]() {
-            if (ld == 0) {
-                if (has_ut) wait_vmcnt<NF * L::NCOPY0>();
-                else wait_vmcnt<NF * (L::NC_W + 1)>();
-            } else {
-                if (has_ut) wait_vmcnt<NF * L::NCOPY1>();
-                else wait_vmcnt<NF * L::NC_W>();
-            }
-        };
-        // Prologue: chunks c_begin .. c_begin + D - 2.  Past the end the loaders
-        // still issue the same number of copies (so that the per-chunk count the
-        // waits rely on is constant), reading the last chunk, into the slot of
-        // the missing chunk: a slot no compute wave reads again.
+                    for (int n = 0; n < NH; ++n)
+                        __builtin_amdgcn_global_load_lds(
+                            (const void *)(kc + (size_t)(RPC * (n0 + n)) * rs + voff),
+                            (__attribute__((address_space(3))) void *)(sl + 1024 * (n0 + n)), 16, 0, 0);
+                } else {
 #pragma unroll
-        for (int i = 0; i < D - 1; ++i) issue(c_begin + i, min(c_begin + i, c_end - 1));
-        for (int c = c_begin; c < c_end; ++c) {
-            wait_oldest();
-            lds_only_barrier();  // chunk c handed to the compute waves
-            // refills the slot of chunk c - 1
-            issue(c + D - 1, min(c + D - 1, c_end - 1));
+                    for (int n = 0; n < NH; ++n)
+                        __builtin_amdgcn_global_load_lds(
+                            (const void *)(kc + (size_t)min(RPC * (n0 + n) + lr, left) * rs + lc),
+                            (__attribute__((address_space(3))) void *)(sl + 1024 * (n0 + n)), 16, 0, 0);
+                }
+                // the gate record (272 bytes), a copy of its own that both waves
+                // issue so that their counts agree
+                if (HF == 0 && l < kGateRec / 4)
+                    __builtin_amdgcn_global_load_lds(
+                        (const void *)(p.gf + ((size_t)bh * p.NC + src) * kGateRec + 4 * l),
+                        (__attribute__((address_space(3))) void *)(sl + L::oD), 16, 0, 0);
+            };
+            const std::integral_constant<int, 0> h0{};
+            const std::integral_constant<int, 1> h1{};
+#pragma unroll
+            for (int i = 0; i < D - 1; ++i) issue(c_begin + i, i * L::SLOT, h0), issue(c_begin + i, i * L::SLOT, h1);
+            issue(c_begin + D - 1, (D - 1) * L::SLOT, h0);
+            int off = 0, prev = (D - 1) * L::SLOT;           // slots of chunks c and c - 1
+            for (int c = c_begin; c < c_end; ++c) {
+                wait_vmcnt<(D - 2) * (NS + 1) + NH + 1>();   // K(c) has landed
+                lds_only_barrier();                          // B1(c)
+                issue(c + D - 1, prev, h1);
+                lds_only_barrier();                          // B2(c): K(c) is in registers
+                issue(c + D, off, h0);
+                prev = off;
+                off = off + L::SLOT == D * L::SLOT ? 0 : off + L::SLOT;
+            }
         }
         wait_vmcnt<0>();
         lds_only_barrier();                     // ring quiet: the compute waves may reuse it
@@ -623,279 +664,301 @@ void gdn_chunkscan_kernel(Params<E> p) {
         return;
     }
 
-    if constexpr (FUSE) {
+    if constexpr (NOW > 0) {
         if (w >= NCW) {
             // ---------------- output waves ----------------
-            // Output wave wo finishes chunk c - 1 after barrier c (and the
-            // last chunk after the final barrier) for the columns of compute
-            // wave wo:  O^T = H_{c-1}^T Qf^T + U^T Pf^T, per token tile rt
-            //   A operands: the handed-off H_{c-1} and U fragments (B-operand
+            // Wave o forms, for token tiles rt = o + NOW j of each chunk and every
+            // column tile,  O^T = H_{c-1}^T Q~^T + U^T P^T:
+            //   A operands: the H_{c-1} and U fragments in LDS (B-operand
             //   layout over d, resp. s, which is also the A layout),
             //   B operands: the Qf / Pf row fragments of the chunk.
-            // Lane (li, lg) gets O[16 rt + li][jw + 16 ct + 4 lg + q].
-            const int wo = w - NCW;
-            const int jw = wbase + 16 * CT * wo;
-            // Operands of chunk c live in register set (c - c_begin) & 1: at
-            // barrier c the wave requests chunk c's and finishes chunk c - 1
-            // from the other set, so a load is consumed one chunk later.
-            frag q0[4][KB], p0[4][2], q1[4][KB], p1[4][2];
-            auto load_ops = [&](int c, frag (&q)[4][KB], frag (&pf)[4][2]) {
-                const size_t cidx = (size_t)bh * p.NC + c;
-                const E *Qf = p.Qf + cidx * (size_t)kChunk * DK + l * 8;
-                const E *Pf = p.Pf + cidx * (size_t)kChunk * kChunk + l * 8;
+            // Lane (li, lg) gets columns 4 lg + q of each tile for token 16 rt + li.
+            constexpr int RO = 4 / NOW;
+            const int o = w - NCW;
+            struct Set {
+                frag q[RO][KB], p[RO][2];
+            };
+            // Operands are requested two chunks ahead, in three register sets
+            // used in turn (past the end: the last chunk's, not used), a part of
+            // them at the start of either phase so that neither waits for the
+            // issue.  Addresses are a uniform base and a 32-bit lane offset.
+            const unsigned lo16 = 16u * l * (sizeof(frag) / 16);
+            const char *qp = (const char *)(p.Qf + ((size_t)bh * p.NC + c_begin) * (size_t)kChunk * DK);
+            const char *pp = (const char *)(p.Pf + ((size_t)bh * p.NC + c_begin) * (size_t)kChunk * kChunk);
+            int c_req = c_begin;                         // chunk that qp and pp point at
+            auto ld = [&](const char *base, int f) { return TR::load8((const E *)(base + f * (int)sizeof(frag) * 64 + lo16)); };
+            auto load_q = [&](Set &st, int kb0, int kb1) {
 #pragma unroll
-                for (int rt = 0; rt < 4; ++rt) {
+                for (int j = 0; j < RO; ++j)
 #pragma unroll
-                    for (int kb = 0; kb < KB; ++kb) q[rt][kb] = TR::load8(Qf + (size_t)(rt * KB + kb) * 512);
+                    for (int kb = kb0; kb < kb1; ++kb) st.q[j][kb] = ld(qp, (o + NOW * j) * KB + kb);
+            };
+            auto load_p = [&](Set &st) {
 #pragma unroll
-                    for (int m = 0; m < 2; ++m)
-                        if (m == 0 || rt >= 2) pf[rt][m] = TR::load8(Pf + (size_t)(rt * 2 + m) * 512);
+                for (int j = 0; j < RO; ++j) {
+                    const int rt = o + NOW * j;
+                    st.p[j][0] = ld(pp, rt * 2);
+                    // block m = 1 (tokens 32 ..) only matters for rt >= 2
+                    if (rt >= 2) st.p[j][1] = ld(pp, rt * 2 + 1);
+                }
+                if (c_req + 1 < c_end) {
+                    ++c_req;
+                    qp += (size_t)kChunk * DK * sizeof(E);
+                    pp += (size_t)kChunk * kChunk * sizeof(E);
                 }
             };
-            auto finish = [&](int c, const frag (&cq)[4][KB], const frag (&cp)[4][2]) {
-                const int i = (c - c_begin) & 1;
-                const int nvalid = min(kChunk, p.T - c * kChunk);
-                const size_t row0 = ((size_t)b * p.T + (size_t)c * kChunk) * p.H + h;
+            const size_t ostride = (size_t)p.H * DV;     // elements from one token's row to the next one's
+            E *obase = p.out + (((size_t)b * p.T + (size_t)c_begin * kChunk) * p.H + h) * DV + jw;
+            unsigned ooff[RO];
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    frag hbf[KB], ubf[2];
+            for (int j = 0; j < RO; ++j) ooff[j] = (unsigned)((16 * (o + NOW * j) + li) * ostride + 4 * CT * lg);
+            auto chunk = [&](int c, Set &st, Set &nx, auto whole) {
+                lds_only_barrier();                      // B1(c)
+                frag hb[CT][KB];
 #pragma unroll
-                    for (int f = 0; f < KB; ++f) hbf[f] = *hoff_at(i, wo, ct, f);
+                for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-                    for (int m = 0; m < 2; ++m) ubf[m] = *hoff_at(i, wo, ct, KB + m);
+                    for (int kb = 0; kb < KB; ++kb) hb[ct][kb] = X::get(hx, ct * KB + kb, l);
+                __builtin_amdgcn_sched_barrier(0);
+                load_q(nx, 0, KB / 2);
+                __builtin_amdgcn_sched_barrier(0);
+                f32x4 acc[RO][CT];
 #pragma unroll
-                    for (int rt = 0; rt < 4; ++rt) {
-                        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-                        for (int kb = 0; kb < KB; ++kb) acc = TR::mma(hbf[kb], cq[rt][kb], acc);
+                    for (int j = 0; j < RO; ++j) {
+                        acc[j][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int m = 0; m < 2; ++m)
-                            if (m == 0 || rt >= 2) acc = TR::mma(ubf[m], cp[rt][m], acc);
-                        const int r = 16 * rt + li;
-                        if (r < nvalid)
-                            TR::store(p.out + (row0 + (size_t)r * p.H) * DV + jw + 16 * ct + 4 * lg, TR::from_f32(acc));
+                        for (int kb = 0; kb < KB; ++kb) acc[j][ct] = TR::mma(hb[ct][kb], st.q[j][kb], acc[j][ct]);
+                    }
+                lds_only_barrier();                      // B2(c)
+                frag ub[CT][2];
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) ub[ct][m] = X::get(uo, ct * 2 + m, l);
+                __builtin_amdgcn_sched_barrier(0);
+                load_q(nx, KB / 2, KB);
+                load_p(nx);
+                __builtin_amdgcn_sched_barrier(0);
+                const int nvalid = p.T - c * kChunk;
+#pragma unroll
+                for (int j = 0; j < RO; ++j) {
+                    const int rt = o + NOW * j;
+                    quad oq[CT];
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) {
+                        acc[j][ct] = TR::mma(ub[ct][0], st.p[j][0], acc[j][ct]);
+                        if (rt >= 2) acc[j][ct] = TR::mma(ub[ct][1], st.p[j][1], acc[j][ct]);
+                        oq[ct] = TR::from_f32(acc[j][ct]);
+                    }
+                    if (decltype(whole)::value || 16 * rt + li < nvalid) {
+                        if constexpr (CT == 2)
+                            TR::store8(obase + ooff[j], TR::cat(oq[0], oq[1]));
+                        else
+                            TR::store(obase + ooff[j], oq[0]);
                     }
                 }
+                obase += kChunk * ostride;
             };
-            for (int c = c_begin; c < c_end; c += 2) {
-                lds_only_barrier();  // barrier c
-                load_ops(c, q0, p0);
-                if (c > c_begin) finish(c - 1, q1, p1);
-                if (c + 1 < c_end) {
-                    lds_only_barrier();  // barrier c + 1
-                    load_ops(c + 1, q1, p1);
-                    finish(c, q0, p0);
-                }
+            Set s0, s1, s2;
+            load_q(s0, 0, KB);
+            load_p(s0);
+            load_q(s1, 0, KB);
+            load_p(s1);
+            // Whole chunks three at a time, without a branch (a branch around the
+            // stores or out of the loop makes the compiler wait for operands that
+            // are not needed yet); the rest, the sequence's last chunk among it,
+            // one by one.
+            const int c_whole = min(c_end, p.T / kChunk);
+            int c = c_begin;
+            for (; c + 3 <= c_whole; c += 3) {
+                chunk(c, s0, s2, std::true_type{});
+                chunk(c + 1, s1, s0, std::true_type{});
+                chunk(c + 2, s2, s1, std::true_type{});
             }
-            lds_only_barrier();  // the compute waves have handed off the last chunk
-            if ((c_end - 1 - c_begin) & 1)
-                finish(c_end - 1, q1, p1);
-            else
-                finish(c_end - 1, q0, p0);
+            if (c < c_end) chunk(c, s0, s2, std::false_type{});
+            if (c + 1 < c_end) chunk(c + 1, s1, s0, std::false_type{});
+            if (c + 2 < c_end) chunk(c + 2, s2, s1, std::false_type{});
+            lds_only_barrier();                          // matches the loaders' last barrier
             return;
         }
     }
 
     // ---------------- compute waves ----------------
-    const int jw = wbase + 16 * CT * w;          // this wave's first column
-    // State H[:, jw + 16 ct + li] as NT accumulator tiles in P32 order:
-    // Hacc[t][ct][q] = H[32 (t / 2) + 8 lg + 4 (t % 2) + q][jw + 16 ct + li].
-    f32x4 Hacc[NT][CT];
-    auto row0 = [&](int t) { return 32 * (t >> 1) + 8 * lg + 4 * (t & 1); };
+    const int s = w;                                     // token tile and share of the row tiles
+    // State H[:, jw + 16 ct + li], row tiles t = RT s + i in P32 order:
+    // Hacc[i][ct][q] = H[32 (t / 2) + 8 lg + 4 (t % 2) + q][jw + 16 ct + li].
+    f32x4 Hacc[RT][CT];
+    auto row0 = [&](int i) {
+        const int t = RT * s + i;
+        return 32 * (t >> 1) + 8 * lg + 4 * (t & 1);
+    };
     if constexpr (PHASE == SCAN_TRANS) {
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int i = 0; i < RT; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    Hacc[t][ct][q] = (is_phi && row0(t) + q == jw + 16 * ct + li) ? 1.f : 0.f;
+                    Hacc[i][ct][q] = (is_phi && row0(i) + q == col(ct)) ? 1.f : 0.f;
     } else if (p.NG > 1) {
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-                Hacc[t][ct] = *(const f32x4 *)(p.HgT + ((size_t)unit * DV + jw + 16 * ct + li) * DK + row0(t));
+            for (int i = 0; i < RT; ++i)
+                Hacc[i][ct] = *(const f32x4 *)(p.HgT + ((size_t)unit * DV + col(ct)) * DK + row0(i));
     } else if (p.state_in) {
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int i = 0; i < RT; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    Hacc[t][ct][q] = p.state_in[((size_t)bh * DK + row0(t) + q) * DV + jw + 16 * ct + li];
+                    Hacc[i][ct][q] = p.state_in[((size_t)bh * DK + row0(i) + q) * DV + col(ct)];
     } else {
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) Hacc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < RT; ++i) Hacc[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    double lgam = 0.0;  // sum of gC over the group
+    double lgam = 0.0;  // sum of gC over the group (SCAN_TRANS)
 
-    // Operands of one chunk, read from its ring slot (fragment layouts below).
-    // With AHEAD the wave reads chunk c + 1's slot while it computes chunk c,
-    // so the LDS latency stays off the chain.
-    struct Ops {
-        frag wf[KB][4], kf[NT][2];
-        typename TR::quad us[4][CT];
-        f32x4 dsc[4];
-        double gC;
-        float gam;
-    };
-    //   -W fragment (wave kb / 2, token tile st, k block kb % 2),
-    //   K^T fragment (row tile t, token block m): rows d in P32 order
-    //     32 (t / 2) + p32_row(t % 2, li), tokens 32 m + 8 lg + e,
-    //   U~t quad of token tile st = 2 m + a: tokens 32 m + 8 lg + 4 a + q
-    //     (zero for Phi columns), and the key scales of the same tokens,
-    //   g_C and gamma = e^{g_C} (broadcast reads).
-    auto read_ops = [&](int c, Ops &o) {
-        const E *sl = slot_of(c);
-        const float *Dl = (const float *)(sl + L::oD);
+    // H rounded to E into LDS, as the B operands over its 32-row blocks; with
+    // the output in its own kernel also the state entering chunk c, to Hs
+    auto put_h = [&](int c) {
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
+        for (int ct = 0; ct < CT; ++ct) {
+            quad hq[RT];
 #pragma unroll
-            for (int st = 0; st < 4; ++st)
-                o.us[st][ct] = has_ut ? TR::load(sl + 2 * L::WK + (size_t)w * CT * 1024 + l * 4 + ct * 1024 + st * 256)
-                                      : TR::zero();
+            for (int i = 0; i < RT; ++i) hq[i] = TR::from_f32(Hacc[i][ct]);
+            if constexpr (RT == 2)
+                X::put2(hx, ct * KB + s, l, hq[0], hq[1]);
+            else
+                X::put(hx, ct * KB + (s >> 1), s & 1, l, hq[0]);
+            if constexpr (PHASE == SCAN_STATES && !NOW) {
+                if (c < c_end) {
+                    E *Hs = p.Hs + (((size_t)bh * p.NC + c) * DV + col(ct)) * DK;
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const int st = 2 * m + a;
-                    o.wf[kb][st] = TR::load8(sl + l * 8 + (((kb >> 1) * 4 + st) * 2 + (kb & 1)) * 512);
+                    for (int i = 0; i < RT; ++i) TR::store(Hs + row0(i), hq[i]);
                 }
+            }
+        }
+    };
+    // this wave's U~t quads: tokens 32 m + 8 lg + 4 a + q (s = 2 m + a); requested
+    // NWS chunks ahead, ut running over the chunks (past the end: the last one)
+    const char *ut = (const char *)(p.Ut + ((size_t)bh * p.NC + c_begin) * (size_t)DV * kChunk) +
+                     (size_t)(jw / 16) * 1024 * sizeof(E);
+    unsigned uoff[CT];                                   // column c sits in lane c % 16 of tile c / 16
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+        const int c = col(ct) - jw;
+        uoff[ct] = (1024 * (c >> 4) + s * 256 + (16 * lg + (c & 15)) * 4) * (unsigned)sizeof(E);
+    }
+    int u_left = c_end - 1 - c_begin;                    // chunks after the one ut points at
+    auto load_us = [&](quad (&us)[CT]) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+            us[ct] = has_ut ? TR::load((const E *)(ut + uoff[ct])) : TR::zero();
+        ut += u_left > 0 ? (size_t)DV * kChunk * sizeof(E) : 0;
+        --u_left;
+    };
+    // -W fragments of token tile s (k block kb of wave-row pair kb / 2), straight
+    // from the workspace: no other wave needs them.  Requested NWS chunks ahead,
+    // like U~t.
+    const char *wp = (const char *)(p.W + ((size_t)bh * p.NC + c_begin) * (size_t)L::WK);
+    const unsigned woff = (s * 1024 + l * 8) * (unsigned)sizeof(E);
+    auto load_w = [&](frag (&wf)[KB]) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+            wf[kb] = TR::load8((const E *)(wp + ((kb >> 1) * 4096 + (kb & 1) * 512) * sizeof(E) + woff));
+        wp += u_left > 0 ? (size_t)L::W_BYTES : 0;
+    };
+    // One chunk: U = U~t - W H_{c-1} (the workspace holds -W), then
+    // H_c = gamma H_{c-1} + K^T (diag(e^{g_C - g}) U).
+    // Chunk c_begin + j sits in slot j % D and its W and U~t in set j % NWS, so with
+    // four steps in a row every LDS address is a constant.
+    auto step = [&](int c, auto j_, quad (&us)[CT], frag (&wf)[KB]) {
+        constexpr int J = decltype(j_)::value;
+        lds_only_barrier();                              // B1(c)
+        const unsigned char *sl = scan_lds + (J % D) * L::SLOT;
+        frag hb[KB][CT], kf[RT][2];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) hb[kb][ct] = X::get(hx, ct * KB + kb, l);
+        const float *Dl = (const float *)(sl + L::oD);
+        const float gam = Dl[kChunk + 2];
+        const f32x4 dsc = *(const f32x4 *)(Dl + 32 * (s >> 1) + 8 * lg + 4 * (s & 1));
+        if constexpr (PHASE == SCAN_TRANS) lgam += *(const double *)(Dl + kChunk);
+        // K^T fragments of the wave's rows: rows d in P32 order 32 (t / 2) +
+        // p32_row(t % 2, li), tokens 32 m + 8 lg + e
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-                o.kf[t][m] = kt_frag<E, DK>(sl + L::WK, 32 * m, 32 * (t >> 1), t & 1, li, lg);
+            for (int i = 0; i < RT; ++i) {
+                const int t = RT * s + i;
+                kf[i][m] = kt_frag<E, DK>((const E *)sl, 32 * m, 32 * (t >> 1), t & 1, li, lg);
+            }
+        f32x4 u[CT];
 #pragma unroll
-        for (int st = 0; st < 4; ++st) o.dsc[st] = *(const f32x4 *)(Dl + 32 * (st >> 1) + 8 * lg + 4 * (st & 1));
-        o.gC = *(const double *)(Dl + kChunk);
-        o.gam = Dl[kChunk + 2];
+        for (int ct = 0; ct < CT; ++ct) u[ct] = TR::to_f32(us[ct]);
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) u[ct] = TR::mma(wf[kb], hb[kb][ct], u[ct]);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            X::put(ux, ct * 2 + (s >> 1), s & 1, l, TR::from_f32(u[ct] * dsc));
+            const quad uq = TR::from_f32(u[ct]);
+            if constexpr (NOW > 0) X::put(uo, ct * 2 + (s >> 1), s & 1, l, uq);
+            if constexpr (PHASE == SCAN_STATES && !NOW)
+                TR::store(p.Us + (((size_t)bh * p.NC + c) * DV + col(ct)) * kChunk + 32 * (s >> 1) + 8 * lg +
+                              4 * (s & 1),
+                          uq);
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) Hacc[i][ct] *= gam;
+        lds_only_barrier();                              // B2(c)
+        frag uk[2][CT];
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) uk[m][ct] = X::get(ux, ct * 2 + m, l);
+        load_w(wf);
+        load_us(us);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) Hacc[i][ct] = TR::mma(kf[i][m], uk[m][ct], Hacc[i][ct]);
+        put_h(c + 1);
     };
-
-    // bf16: the U~t seeds enter the accumulators through an MFMA with a 0/1
-    // selection operand (exact: one product 1 x u per entry), so no VALU
-    // unpacking sits before the first W H MFMA.  sel[a] places the 32-token
-    // B fragment cat(us[2 m], us[2 m + 1]) (lane (li, lg): tokens 32 m + 8 lg
-    // + e') in the rows of tile 2 m + a, i.e. tile row i takes token
-    // 32 m + p32_row(a, i): lane (li, lg) of sel[a] holds 1 at e' = 4 a +
-    // li % 4 when lg = li / 4, else 0.
-    frag sel[2];
+    quad us[NWS][CT];
+    frag wf[NWS][KB];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-        if (lg == (li >> 2)) {
-            if (a == 0) lo[li & 3] = 1.f;
-            else hi[li & 3] = 1.f;
-        }
-        sel[a] = TR::cat(TR::from_f32(lo), TR::from_f32(hi));
+    for (int i = 0; i < NWS; ++i) {
+        load_w(wf[i]);
+        load_us(us[i]);
     }
-
-    // One chunk: U = U~t - W H_{c-1} (the workspace holds -W), then
-    // H_c = gamma H_{c-1} + K^T (diag(e^{g_C - g}) U).  The chain per token
-    // half m: its W H MFMAs, the conversion of its U half (as is, for the
-    // output, and scaled by e^{g_C - g}, for the update), then that half's
-    // update.  Half 0 is finished first, so its conversion overlaps the MFMAs
-    // of half 1, and half 1's conversion those of the first update.  The
-    // output wave's operands (H_{c-1}, then each U half) are handed off as
-    // soon as they exist, so the stores have drained by the next barrier.
-    auto step = [&](int c, const Ops &o) {
-        const size_t cidx = (size_t)bh * p.NC + c;
-        const int i = (c - c_begin) & 1;
-        // H_{c-1} rounded to E: B operands over the KB 32-row blocks.
-        frag hb[KB][CT];
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                hb[kb][ct] = TR::cat(TR::from_f32(Hacc[2 * kb][ct]), TR::from_f32(Hacc[2 * kb + 1][ct]));
-                if constexpr (FUSE) *hoff_at(i, w, ct, kb) = hb[kb][ct];
-            }
-        lgam += o.gC;
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) Hacc[t][ct] *= o.gam;
-        f32x4 part[4][CT];
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int st = 0; st < 4; ++st) {
-                if constexpr (sizeof(E) == 2)
-                    part[st][ct] = TR::mma(sel[st & 1], TR::cat(o.us[st & 2][ct], o.us[(st & 2) + 1][ct]),
-                                           f32x4{0.f, 0.f, 0.f, 0.f});
-                else
-                    part[st][ct] = TR::to_f32(o.us[st][ct]);
-            }
-        frag ub[2][CT], uk[2][CT];
-        auto wh_half = [&](int m) {
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int ct = 0; ct < CT; ++ct)
-                        part[2 * m + a][ct] = TR::mma(o.wf[kb][2 * m + a], hb[kb][ct], part[2 * m + a][ct]);
-        };
-        auto cvt_half = [&](int m) {
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                ub[m][ct] = TR::cat(TR::from_f32(part[2 * m][ct]), TR::from_f32(part[2 * m + 1][ct]));
-                uk[m][ct] = TR::cat(TR::from_f32(part[2 * m][ct] * o.dsc[2 * m]),
-                                    TR::from_f32(part[2 * m + 1][ct] * o.dsc[2 * m + 1]));
-                if constexpr (FUSE) *hoff_at(i, w, ct, KB + m) = ub[m][ct];
-            }
-        };
-        auto kt_half = [&](int m) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int ct = 0; ct < CT; ++ct) Hacc[t][ct] = TR::mma(o.kf[t][m], uk[m][ct], Hacc[t][ct]);
-        };
-        wh_half(0);
-        wh_half(1);
-        cvt_half(0);
-        kt_half(0);
-        cvt_half(1);
-        kt_half(1);
-        if constexpr (PHASE == SCAN_STATES && !FUSE) {
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
-                    TR::store8(p.Hs + cidx * (size_t)DV * DK + (size_t)(jw + 16 * ct + li) * DK + 32 * kb + 8 * lg,
-                               hb[kb][ct]);
-                E *Us = p.Us + cidx * (size_t)DV * kChunk + (size_t)(jw + 16 * ct + li) * kChunk + 8 * lg;
-                TR::store8(Us, ub[0][ct]);
-                TR::store8(Us + 32, ub[1][ct]);
-            }
-        }
-    };
-
-    // Barrier c hands over chunk c (and, with AHEAD, chunk c + 1: the loaders
-    // wait one chunk further).  Operand sets alternate between chunks.
-    Ops opA, opB;
-    for (int c = c_begin; c < c_end; c += 2) {
-        lds_only_barrier();  // barrier c
-        if constexpr (AHEAD) {
-            if (c == c_begin) read_ops(c, opA);
-            read_ops(c + 1, opB);  // past the end: a padding slot, not used
-        } else {
-            read_ops(c, opA);
-        }
-        step(c, opA);
-        if (c + 1 >= c_end) break;
-        lds_only_barrier();  // barrier c + 1
-        if constexpr (AHEAD)
-            read_ops(c + 2, opA);
-        else
-            read_ops(c + 1, opB);
-        step(c + 1, opB);
+    put_h(c_begin);
+    int c = c_begin;
+    const std::integral_constant<int, 0> j0{};
+    const std::integral_constant<int, 1> j1{};
+    const std::integral_constant<int, 2> j2{};
+    const std::integral_constant<int, 3> j3{};
+    for (; c + 4 <= c_end; c += 4) {
+        step(c, j0, us[0 % NWS], wf[0 % NWS]);
+        step(c + 1, j1, us[1 % NWS], wf[1 % NWS]);
+        step(c + 2, j2, us[2 % NWS], wf[2 % NWS]);
+        step(c + 3, j3, us[3 % NWS], wf[3 % NWS]);
     }
+    if (c < c_end) step(c, j0, us[0 % NWS], wf[0 % NWS]);
+    if (c + 1 < c_end) step(c + 1, j1, us[1 % NWS], wf[1 % NWS]);
+    if (c + 2 < c_end) step(c + 2, j2, us[2 % NWS], wf[2 % NWS]);
     lds_only_barrier();  // the loaders have drained: the ring is free
 
     const size_t gidx = (size_t)bh * p.NG + grp;
@@ -904,18 +967,18 @@ void gdn_chunkscan_kernel(Params<E> p) {
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
+                for (int i = 0; i < RT; ++i)
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        p.state_out[((size_t)bh * DK + row0(t) + q) * DV + jw + 16 * ct + li] = Hacc[t][ct][q];
+                        p.state_out[((size_t)bh * DK + row0(i) + q) * DV + col(ct)] = Hacc[i][ct][q];
         }
     } else if (!is_phi) {  // SCAN_TRANS from here on
         // Psi_g^T [Dv][Dk], fp32
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-                *(f32x4 *)(p.PsiT + (gidx * DV + jw + 16 * ct + li) * DK + row0(t)) = Hacc[t][ct];
+            for (int i = 0; i < RT; ++i)
+                *(f32x4 *)(p.PsiT + (gidx * DV + col(ct)) * DK + row0(i)) = Hacc[i][ct];
     } else {
         if (jb == 0 && w == 0 && l == 0) p.lgam[gidx] = lgam;
         // N_g = Phi_g - Gamma_g I, rounded to E, staged in LDS (in the ring
@@ -923,24 +986,21 @@ void gdn_chunkscan_kernel(Params<E> p) {
         // re-read with the transposing LDS read into the group scan's A-operand
         // fragments: fragment (wave v, row tile t, k block kb), lane (li, lg) =
         //   N[64 v + 32 (t / 2) + p32_row(t % 2, li)][32 kb + 8 lg + e].
-        static_assert(WGC % 32 == 0, "the transfer pass writes whole 32-column k blocks");
+        static_assert(PHASE != SCAN_TRANS || WGC % 32 == 0, "the transfer pass writes whole 32-column k blocks");
         constexpr int LDN = DK + 16 / (int)sizeof(E);
-        static_assert(sizeof(E) * WGC * LDN <= L::bytes, "N^T staging");
+        static_assert((int)sizeof(E) * WGC * LDN <= L::oH, "N^T staging");
         const float Gam = expf((float)lgam);
-        E *sN = ring;
+        E *sN = (E *)scan_lds;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-            const int e = 16 * CT * w + 16 * ct + li;  // staging row
+            const int e = col(ct) - jw;                  // staging row
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                f32x4 lo = Hacc[2 * kb][ct], hi = Hacc[2 * kb + 1][ct];
-                const int r0 = 32 * kb + 8 * lg;
+            for (int i = 0; i < RT; ++i) {
+                f32x4 n = Hacc[i][ct];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (r0 + q == col0 + e) lo[q] -= Gam;
-                    if (r0 + 4 + q == col0 + e) hi[q] -= Gam;
-                }
-                TR::store8(sN + e * LDN + r0, TR::cat(TR::from_f32(lo), TR::from_f32(hi)));
+                for (int q = 0; q < 4; ++q)
+                    if (row0(i) + q == col0 + e) n[q] -= Gam;
+                TR::store(sN + e * LDN + row0(i), TR::from_f32(n));
             }
         }
         lds_only_barrier();  // staging written (the loaders take this barrier too)
