@@ -274,7 +274,7 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
     auto stage = [&](int i) -> hipError_t {
         switch (i) {
         case 0:
-            return launch((const void *)gdn::gdn_wy_kernel<E, DK, DV>, dim3(p.NC, BH), dim3(64 * gdn::kWyWaves),
+            return launch((const void *)gdn::gdn_wy_kernel<E, DK, DV>, dim3(p.NC * BH), dim3(64 * gdn::kWyWaves),
                           lds1, s, p);
         case 1:
             return launch(scant, dim3(groups((DK + DV) / 32, BH * p.NG)), dim3(gdn::scan_threads<0>()), LT::bytes, s, p);
