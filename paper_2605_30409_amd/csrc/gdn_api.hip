@@ -279,8 +279,8 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
         case 1:
             return launch(scant, dim3(groups((DK + DV) / 32, BH * p.NG)), dim3(gdn::scan_threads<0>()), LT::bytes, s, p);
         case 2:
-            return launch((const void *)gdn::gdn_groupscan_kernel<E, DK, DV>, dim3(groups(DV / 16, BH)), dim3(DK),
-                          0, s, p);
+            return launch((const void *)gdn::gdn_groupscan_kernel<E, DK, DV>, dim3(groups(DV / 16, BH)),
+                          dim3(64 * gdn::kScanSplit), 0, s, p);
         case 3:
             if (wide)
                 return launch(scan2, dim3(groups(DV / (16 * CTW), BH * p.NG)), dim3(gdn::scan_threads<NOW>()), L2::bytes, s, p);

@@ -1023,89 +1023,101 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
 
 // --------------------------------------------------------------------------
 // Group scan: H <- Gamma_g H + N_g H + Psi_g over the groups of one (b, h), in
-// 16-column blocks (one workgroup each, Dk/64 waves splitting the rows, which
-// exchange their halves of H each step through LDS).  Records every group's
-// entry state H^T for the state stage and writes the final state.
+// 16-column blocks (one workgroup each, four waves splitting the rows, which
+// exchange their shares of H each step through LDS).  Records every group's
+// entry state H^T for the state stage and writes the final state.  A step is
+// short next to the latency of its operands (N_g alone is 32 KB in bf16), so
+// they are requested four groups ahead, in four register sets used in turn:
+// with one group's notice the step took 1.85 us (bf16, D = 128).
 // --------------------------------------------------------------------------
 template <class E, int DK, int DV>
-__global__ __launch_bounds__(DK) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ __launch_bounds__(64 * kScanSplit) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gdn_groupscan_kernel(Params<E> p) {
     using TR = Tr<E>;
+    using X = Xch<E>;
     using frag = typename TR::frag;
-    constexpr int NW = DK / 64;
+    using quad = typename TR::quad;
+    constexpr int RT = DK / 16 / kScanSplit;             // row tiles per wave
     constexpr int NJ = DV / 16;
     constexpr int KB = DK / 32;
-    __shared__ frag sH[2][NW][2][64];  // bf16 halves of H, double-buffered
+    __shared__ __align__(16) unsigned char sH[2][KB * X::BYTES];  // H rounded to E, double-buffered
 
     const int id = blockIdx.x, x = id & 7, slot = id >> 3;
     const int bh = (slot / NJ) * 8 + x, jt = slot % NJ;
     if (bh >= p.B * p.H) return;
-    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, li = l & 15, lg = l >> 4;
-    const int d0 = 64 * w;
+    const int tid = threadIdx.x, s = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, li = l & 15, lg = l >> 4;
     const int j = 16 * jt + li;
+    auto row0 = [&](int i) {
+        const int t = RT * s + i;
+        return 32 * (t >> 1) + 8 * lg + 4 * (t & 1);
+    };
 
-    f32x4 Hacc[4];
+    f32x4 Hacc[RT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            Hacc[t][q] = p.state_in ? p.state_in[((size_t)bh * DK + d0 + 32 * (t >> 1) + 8 * lg +
-                                                  4 * (t & 1) + q) * DV + j]
-                                    : 0.f;
-    frag nf[4][KB];
-    f32x4 ps[4];
-    double lg_g;
-    auto fetch = [&](int g) {
-        const size_t gidx = (size_t)bh * p.NG + g;
-        const E *Nc = p.Nf + gidx * (size_t)DK * DK + (size_t)w * 4 * KB * 512 + l * 8;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) nf[t][kb] = TR::load8(Nc + (t * KB + kb) * 512);
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            ps[t] = *(const f32x4 *)(p.PsiT + (gidx * DV + j) * DK + d0 + 32 * (t >> 1) + 8 * lg + 4 * (t & 1));
-        lg_g = p.lgam[gidx];
+            Hacc[i][q] = p.state_in ? p.state_in[((size_t)bh * DK + row0(i) + q) * DV + j] : 0.f;
+    struct Set {
+        frag nf[RT][KB];
+        f32x4 ps[RT];
+        double lg;
     };
-    fetch(0);
-    for (int g = 0; g < p.NG; ++g) {
-        const size_t gidx = (size_t)bh * p.NG + g;
-        // entry state of group g
+    auto fetch = [&](int g, Set &o) {                    // past the end: the last group's, not used
+        const size_t gidx = (size_t)bh * p.NG + min(g, p.NG - 1);
+        const E *Nc = p.Nf + gidx * (size_t)DK * DK + (size_t)RT * s * KB * 512 + l * 8;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-            *(f32x4 *)(p.HgT + (gidx * DV + j) * DK + d0 + 32 * (t >> 1) + 8 * lg + 4 * (t & 1)) = Hacc[t];
-        frag hb[KB];
-        const frag own0 = TR::cat(TR::from_f32(Hacc[0]), TR::from_f32(Hacc[1]));
-        const frag own1 = TR::cat(TR::from_f32(Hacc[2]), TR::from_f32(Hacc[3]));
-        if constexpr (NW > 1) {
-            const int buf = g & 1;
-            sH[buf][w][0][l] = own0;
-            sH[buf][w][1][l] = own1;
-            lds_barrier();
-            hb[2 * w] = own0;
-            hb[2 * w + 1] = own1;
-            hb[2 * (1 - w)] = sH[buf][1 - w][0][l];
-            hb[2 * (1 - w) + 1] = sH[buf][1 - w][1][l];
-        } else {
-            hb[0] = own0;
-            hb[1] = own1;
+        for (int i = 0; i < RT; ++i) {
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) o.nf[i][kb] = TR::load8(Nc + (i * KB + kb) * 512);
+            o.ps[i] = *(const f32x4 *)(p.PsiT + (gidx * DV + j) * DK + row0(i));
         }
-        const float Gam = expf((float)lg_g);
+        o.lg = p.lgam[gidx];
+    };
+    auto step = [&](int g, Set &o) {
+        unsigned char *sh = sH[g & 1];
+        float *Hg = p.HgT + (((size_t)bh * p.NG + g) * DV + j) * DK;   // entry state of group g
+        quad hq[RT];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) Hacc[t] = Hacc[t] * Gam + ps[t];
+        for (int i = 0; i < RT; ++i) {
+            hq[i] = TR::from_f32(Hacc[i]);
+            if constexpr (RT == 1) X::put(sh, s >> 1, s & 1, l, hq[0]);
+        }
+        if constexpr (RT == 2) X::put2(sh, s, l, hq[0], hq[1]);
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+        for (int i = 0; i < RT; ++i) *(f32x4 *)(Hg + row0(i)) = Hacc[i];
+        lds_only_barrier();
+        const float Gam = expf((float)o.lg);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) Hacc[t] = TR::mma(nf[t][kb], hb[kb], Hacc[t]);
-        fetch(min(g + 1, p.NG - 1));
+        for (int i = 0; i < RT; ++i) Hacc[i] = Hacc[i] * Gam + o.ps[i];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            const frag hb = X::get(sh, kb, l);
+#pragma unroll
+            for (int i = 0; i < RT; ++i) Hacc[i] = TR::mma(o.nf[i][kb], hb, Hacc[i]);
+        }
+        fetch(g + 4, o);
+    };
+    Set o0, o1, o2, o3;
+    fetch(0, o0);
+    fetch(1, o1);
+    fetch(2, o2);
+    fetch(3, o3);
+    int g = 0;
+    for (; g + 4 <= p.NG; g += 4) {
+        step(g, o0);
+        step(g + 1, o1);
+        step(g + 2, o2);
+        step(g + 3, o3);
     }
+    if (g < p.NG) step(g, o0);
+    if (g + 1 < p.NG) step(g + 1, o1);
+    if (g + 2 < p.NG) step(g + 2, o2);
     if (p.state_out) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int i = 0; i < RT; ++i)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                p.state_out[((size_t)bh * DK + d0 + 32 * (t >> 1) + 8 * lg + 4 * (t & 1) + q) * DV + j] =
-                    Hacc[t][q];
+            for (int q = 0; q < 4; ++q) p.state_out[((size_t)bh * DK + row0(i) + q) * DV + j] = Hacc[i][q];
     }
 }
 
