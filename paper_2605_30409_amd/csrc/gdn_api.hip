@@ -178,6 +178,7 @@ gdn::Params<E> make_params(const void *q, const void *k, const void *v, const fl
     p.H = H;
     p.T = T;
     p.NC = num_chunks(T);
+    p.c0 = 0;
     p.G = G;
     p.NG = (p.NC + G - 1) / G;
     const WsLayout L = ws_layout(B, H, T, Dk, Dv, sizeof(E), G);
@@ -313,6 +314,50 @@ hipError_t dispatch(const gdn::Params<E> &p, int Dk, int Dv, hipStream_t s, Stag
     return launch_path<E, 64, 128>(p, s, tm);
 }
 
+// A single-group call whose chunk records (W, U~, Q~, P: 56 KB a chunk and head at
+// D = 128) outgrow the 256 MB memory-side cache is run in slabs of consecutive
+// chunks that do not: the WY kernel and the scan of one slab, then the next
+// one's in the same records, the state carried in fp32 through the workspace
+// (the records past the first slab are free).  The scan then reads the records
+// from that cache and not from HBM, which takes them in and out at half the
+// speed the scan needs.  Same kernels, same order of every sum: same bits.
+// Measured (us a call, one pass -> slabs): T = 12288, H = 16 271 -> 207, T = 16384
+// 388 -> 269, T = 42240, H = 32 1231 -> 1008, 80 heads of D = 64 at T = 10560
+// 358 -> 303.  Slabs of 112 MB: 104 to 128 are equal, 88 and 160 up to 5 and 14 %
+// slower, 40 no gain (each slab's launches and ring fill cost some 8 us).  Below
+// 144 MB in all it makes no difference.  Fewer than 16 chunks to a slab (more
+// than 127 heads) would pay more for the carried state than it saves; the fp32
+// path is bound by its MFMAs and gains nothing.
+constexpr long long kSlabBytes = 112LL << 20, kSlabsFrom = 144LL << 20;
+
+// Chunks per slab (NC: one pass).  Two slabs or more leave NC / 2 - 1 >= 7 chunks
+// of W records for the carried state, which takes Dv / 32 <= 4.
+template <class E> int slab_chunks(const gdn::Params<E> &p, int Dk, int Dv) {
+    if (sizeof(E) != 2 || p.NG > 1) return p.NC;
+    const long long col = 2LL * kChunk * (2 * Dk + Dv + kChunk) * p.B * p.H, most = kSlabBytes / col;
+    if (col * p.NC <= kSlabsFrom || most < 16) return p.NC;
+    const long long n = (p.NC + most - 1) / most;
+    return (int)((p.NC + n - 1) / n);
+}
+
+// The whole call; with stage timing always in one pass.
+template <class E>
+hipError_t run_slabs(const gdn::Params<E> &p, int Dk, int Dv, hipStream_t s, StageTiming *tm) {
+    const int SC = slab_chunks(p, Dk, Dv);
+    if (tm || SC >= p.NC) return dispatch(p, Dk, Dv, s, tm);
+    float *carry = (float *)(p.W + (size_t)p.B * p.H * SC * kChunk * Dk);
+    hipError_t e = hipSuccess;
+    for (int c0 = 0; c0 < p.NC && e == hipSuccess; c0 += SC) {
+        gdn::Params<E> r = p;
+        r.c0 = c0;
+        r.NC = r.G = p.NC - c0 < SC ? p.NC - c0 : SC;
+        if (c0) r.state_in = carry;
+        if (c0 + SC < p.NC) r.state_out = carry;
+        e = dispatch(r, Dk, Dv, s, tm);
+    }
+    return e;
+}
+
 int run(const void *q, const void *k, const void *v, const float *alpha, const float *beta,
         const float *state_in, void *out, float *state_out, int B, int H, int T, int Dk, int Dv,
         int chunk, bool bf16, int group, void *ws, size_t ws_bytes, void *stream, StageTiming *tm) {
@@ -325,11 +370,11 @@ int run(const void *q, const void *k, const void *v, const float *alpha, const f
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (bf16) {
-        e = dispatch(make_params<uint16_t>(q, k, v, alpha, beta, state_in, out, state_out, B, H, T,
+        e = run_slabs(make_params<uint16_t>(q, k, v, alpha, beta, state_in, out, state_out, B, H, T,
                                            Dk, Dv, G, ws),
                      Dk, Dv, s, tm);
     } else {
-        e = dispatch(make_params<float>(q, k, v, alpha, beta, state_in, out, state_out, B, H, T, Dk,
+        e = run_slabs(make_params<float>(q, k, v, alpha, beta, state_in, out, state_out, B, H, T, Dk,
                                         Dv, G, ws),
                      Dk, Dv, s, tm);
     }

@@ -53,6 +53,7 @@ template <class E> struct Params {
     E *out;
     float *state_out;
     int B, H, T, NC;
+    int c0;           // first chunk of this launch; chunk indices below count from it, up to NC
     int G, NG;        // chunks per scan group, number of groups
     double *g;
     float *gf;        // per (b*H + h, chunk): e^{g_C - g_r} [64], g_C (fp64), e^{g_C}, 1 unused
@@ -139,7 +140,7 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
     // w is wave-uniform: scalar branches and table lookups
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, li = l & 15,
               lg = l >> 4;
-    const int t0 = c * kChunk;
+    const int t0 = (p.c0 + c) * kChunk;
     const int nvalid = min(kChunk, p.T - t0);
     const size_t cidx = (size_t)bh * p.NC + c;
     const size_t row0 = ((size_t)b * p.T + t0) * p.H + h;  // token-row index of token t0
@@ -624,7 +625,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
             const char *kbase = (const char *)(p.k + ((size_t)b * p.T * p.H + h) * DK);
             auto issue = [&](int c, int off, auto half) {
                 constexpr int HF = decltype(half)::value;
-                const int src = min(c, c_end - 1), t0 = src * kChunk, left = p.T - 1 - t0, n0 = NS * part + NH * HF;
+                const int src = min(c, c_end - 1), t0 = (p.c0 + src) * kChunk, left = p.T - 1 - t0, n0 = NS * part + NH * HF;
                 unsigned char *sl = scan_lds + off;
                 const char *kc = kbase + (size_t)t0 * rs;
                 if (left >= kChunk - 1) {
@@ -713,7 +714,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
                 }
             };
             const size_t ostride = (size_t)p.H * DV;     // elements from one token's row to the next one's
-            E *obase = p.out + (((size_t)b * p.T + (size_t)c_begin * kChunk) * p.H + h) * DV + jw;
+            E *obase = p.out + (((size_t)b * p.T + (size_t)(p.c0 + c_begin) * kChunk) * p.H + h) * DV + jw;
             unsigned ooff[RO];
 #pragma unroll
             for (int j = 0; j < RO; ++j) ooff[j] = (unsigned)((16 * (o + NOW * j) + li) * ostride + 4 * CT * lg);
@@ -746,7 +747,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
                 load_q(nx, KB / 2, KB);
                 load_p(nx);
                 __builtin_amdgcn_sched_barrier(0);
-                const int nvalid = p.T - c * kChunk;
+                const int nvalid = p.T - (p.c0 + c) * kChunk;
 #pragma unroll
                 for (int j = 0; j < RO; ++j) {
                     const int rt = o + NOW * j;
@@ -775,7 +776,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
             // stores or out of the loop makes the compiler wait for operands that
             // are not needed yet); the rest, the sequence's last chunk among it,
             // one by one.
-            const int c_whole = min(c_end, p.T / kChunk);
+            const int c_whole = min(c_end, p.T / kChunk - p.c0);
             int c = c_begin;
             for (; c + 3 <= c_whole; c += 3) {
                 chunk(c, s0, s2, std::true_type{});
@@ -1157,7 +1158,7 @@ __global__ __launch_bounds__(256) void gdn_output_kernel(Params<E> p) {
     const int c = blockIdx.x, bh = blockIdx.y;
     const int b = bh / p.H, h = bh - b * p.H;
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, li = l & 15, lg = l >> 4;
-    const int t0 = c * kChunk;
+    const int t0 = (p.c0 + c) * kChunk;
     const int nvalid = min(kChunk, p.T - t0);
     const size_t cidx = (size_t)bh * p.NC + c;
     const size_t row0 = ((size_t)b * p.T + t0) * p.H + h;
