@@ -280,15 +280,12 @@ FRAME_KERNELS = {"summaries": "gdn_frame_summary_kernel", "reduce": "gdn_frame_r
 
 def frame_algorithmic_counts(B, F, N, H, Dk, Dv, NS, esz=2, norm=False, bidir=False, fused=False):
     """See below; with fused and esz = 4 (the fp32 operator) the workspace also
-    carries the four feature maps (written once, each read once) and the gated
-    readout (written and read once)."""
+    carries the two key feature maps (written once, each read once)."""
     r = _frame_counts(B, F, N, H, Dk, Dv, NS, esz, norm, bidir, fused)
     if fused and esz == 4:
         n = B * F * N * H
-        r["workspace"]["summaries"]["written"] += 4 * n * Dk * 4
+        r["workspace"]["summaries"]["written"] += 2 * n * Dk * 4
         r["workspace"]["summaries"]["read"] += 2 * n * Dk * 4
-        r["workspace"]["output"]["read"] += 2 * n * Dk * 4 + n * Dv * 4
-        r["workspace"]["output"]["written"] += n * Dv * 4
     return r
 
 
@@ -455,8 +452,9 @@ def run_frame(args, torch, gdn, dev, to_dev, timed, norm=False, bidir=False, fus
         traffic = None
     kernels = dict(FRAME_KERNELS)
     if fused and f32:
-        kernels.update({"summaries": "gdn_frame_features_kernel + 2 x gdn_frame_summary_kernel<float>",
-                        "output": "gdn_frame_output_f32_fused_kernel + gdn_frame_project_f32_kernel"})
+        kernels.update({"summaries": "gdn_frame_rope_kernel + gdn_frame_kfeatures_kernel + "
+                                     "2 x gdn_frame_summary_kernel<float>",
+                        "output": "gdn_frame_output_fused32_kernel"})
     elif fused:
         kernels.update({"summaries": "gdn_frame_summary_fused_kernel", "output": "gdn_frame_output_fused_kernel"})
     peak = PEAK_F32_TFLOPS if f32 else PEAK_BF16_TFLOPS

@@ -451,7 +451,7 @@ int gdn_frame_profile_stages_fused(const void *q_raw, const void *k_raw, const v
  * every feature, product and readout in fp32 (no bf16 rounding anywhere; the
  * rotation angles in fp64 with accurate sines and cosines).  Arguments,
  * layouts, aliasing rules and errors as the bf16 calls.  The workspace also
- * holds the four feature maps and the gated readout (about
+ * holds the key features and the rotation table (sized at
  * 4 B T H (4 Dk + Dv) bytes on top): size it with
  * gdn_frame_fused_workspace_bytes(..., is_bf16 = 0, ...).
  * gdn_frame_profile_stages_fused_f32 times four stages: features and

@@ -482,7 +482,7 @@ struct FrameArgs {
 };
 
 struct FrameWs {
-    size_t PG, PA, Gf, Af, Hf, Hb, PGz, Gzf, FQT, FQH, FKT, FKH, Y, total;
+    size_t PG, PA, Gf, Af, Hf, Hb, PGz, Gzf, FQ, FKT, FKH, total;
 };
 
 int frame_blocks(int N) { return (N + 63) / 64; }
@@ -504,8 +504,11 @@ int frame_splits(long long units, int N, int token_splits) {
 // backward histories have room for the normalizer's extra 16-column tile; the
 // histories are used by the bidirectional form only, the unrotated-key Gram
 // fragments and their partials by the fused operator only.  The fused
-// operator in fp32 also keeps its feature maps and gated readout (ntok_feat =
-// its B F N H token rows; 0 otherwise).
+// operator in fp32 also keeps its key features and its rotation table (ntok_feat =
+// its B F N H token rows; 0 otherwise): the table, F + max(latent rows, columns)
+// <= F + N rows of Dk floats, fits the first of these regions (2 ntok_feat rows).
+// That region and the unused space at the end once held the query features and
+// the gated readout; the total stays, so a workspace is sized the same as ever.
 FrameWs frame_ws_layout(int B, int H, int F, int Dk, int Dv, size_t esz, int NS, size_t ntok_feat = 0) {
     const size_t bhf = (size_t)B * H * F;
     const size_t DVn = (size_t)Dv + 16;
@@ -521,11 +524,10 @@ FrameWs frame_ws_layout(int B, int H, int F, int Dk, int Dv, size_t esz, int NS,
     L.Hb = off; off = align256(off + bhf * Dk * DVn * 4);
     L.PGz = off; off = align256(off + bhf * np * Dk * Dk * 4);
     L.Gzf = off; off = align256(off + bhf * Dk * Dk * esz);
-    L.FQT = off; off = align256(off + ntok_feat * Dk * 4);
-    L.FQH = off; off = align256(off + ntok_feat * Dk * 4);
+    L.FQ = off;  off = align256(align256(off + ntok_feat * Dk * 4) + ntok_feat * Dk * 4);
     L.FKT = off; off = align256(off + ntok_feat * Dk * 4);
     L.FKH = off; off = align256(off + ntok_feat * Dk * 4);
-    L.Y = off;   off = align256(off + ntok_feat * Dv * 4);
+    off = align256(off + ntok_feat * Dv * 4);
     L.total = off;
     return L;
 }
@@ -643,12 +645,10 @@ gdn::FrameParams<E> make_frame_params(const FrameArgs &a, int NS, void *ws) {
     p.Hb = (float *)(base + L.Hb);
     p.PGz = (float *)(base + L.PGz);
     p.Gzf = (E *)(base + L.Gzf);
-    p.fqt = (float *)(base + L.FQT);
-    p.fqh = (float *)(base + L.FQH);
+    p.rope = (float *)(base + L.FQ);
     p.fkt = (float *)(base + L.FKT);
     p.fkh = (float *)(base + L.FKH);
-    p.ybuf = (float *)(base + L.Y);
-    p.sum_mode = 0;
+    p.no_z = 0;
     p.gate = (const E *)a.gate;
     p.w_o = (const E *)a.w_o;
     p.gain_q = a.gain_q;
@@ -741,56 +741,61 @@ hipError_t launch_frame(const gdn::FrameParams<E> &p, hipStream_t s, int reps, h
     return er;
 }
 
-// The fused operator in fp32: features, then the summaries on the rotated keys
-// (G, A) and on the unrotated ones (the normalizer's Gram matrix and K~^T beta),
-// the fused reduction and scan, and the fp32 output and projection.  The four
+// The fused operator in fp32: the rotation table and the key features, then the
+// summaries on the rotated keys (G, A) and on the unrotated ones (the normalizer's
+// Gram matrix and K~^T beta), the fused reduction and scan, and the fp32 output
+// (query features, readout, gate, projection).  The four
 // profiled stages are: features and summaries, reduction, scan, output and
 // projection.
 template <int DK, int DV, bool BIDIR>
 hipError_t launch_frame_fused32(const gdn::FrameParams<float> &p, hipStream_t s, int reps, hipEvent_t *ev) {
     using E = float;
     using LS = gdn::FrameSumLds<E, DK, DV, false>;
-    using LO = gdn::FrameOutLds<E, DK, DV, true>;
-    using LP = gdn::ProjectLds<DV>;
+    using LO = gdn::FusedOut32Lds<DK, DV>;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] {
         hipError_t e = hipFuncSetAttribute((const void *)gdn::gdn_frame_summary_kernel<E, DK, DV, true, false>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)LS::bytes);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)gdn::gdn_frame_output_f32_fused_kernel<DK, DV>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LO::bytes);
+            e = hipFuncSetAttribute((const void *)gdn::gdn_frame_summary_kernel<E, DK, DV, true, false, true>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LS::bytes);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)gdn::gdn_frame_project_f32_kernel<DV>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LP::bytes);
+            e = hipFuncSetAttribute((const void *)gdn::gdn_frame_output_fused32_kernel<DK, DV>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LO::bytes);
         attr_err = e;
     });
     if (attr_err != hipSuccess) return attr_err;
     const long long BH = (long long)p.B * p.H, units = BH * p.F;
     constexpr int NJ = DV / 16 + 1;
     constexpr int NI = (DK / 16) * (DK / 32) * 2 + (DK / 16) * NJ;
-    const size_t rows = 2 * (size_t)BH * p.F * p.N;                 // q and k rows
-    const size_t feat_blocks = (rows + 4 * (128 / DK) - 1) / (4 * (128 / DK));
+    const size_t rows = (size_t)BH * p.F * p.N;                     // key rows
+    const size_t feat_blocks = (rows * (DK / 4) + 255) / 256;
+    const int lat_rows = 1 + (p.N - 1) / p.lat_w, lat_cols = p.N < p.lat_w ? p.N : p.lat_w;
+    int rope_rows = p.F + (lat_rows > lat_cols ? lat_rows : lat_cols);
     auto stage = [&](int i) -> hipError_t {
         switch (i) {
         case 0: {
-            hipError_t e = launch((const void *)gdn::gdn_frame_features_kernel<DK>, dim3((unsigned)feat_blocks),
-                                  dim3(256), 0, s, p);
+            gdn::FrameParams<E> copy = p;
+            void *args[] = {&copy, &rope_rows};
+            hipError_t e = hipLaunchKernel((const void *)gdn::gdn_frame_rope_kernel<DK>,
+                                           dim3((unsigned)(((long long)rope_rows * (DK / 2) + 255) / 256)), dim3(256), args,
+                                           0, s);
+            if (e == hipSuccess)
+                e = launch((const void *)gdn::gdn_frame_kfeatures_kernel<DK>, dim3((unsigned)feat_blocks), dim3(256), 0, s,
+                           p);
             // rotated keys: G and the A tiles
             gdn::FrameParams<E> pr = p;
             pr.k = p.fkh;
-            pr.sum_mode = 1;
+            pr.no_z = 1;
             if (e == hipSuccess)
                 e = launch((const void *)gdn::gdn_frame_summary_kernel<E, DK, DV, true, false>,
                            dim3((unsigned)(units * p.NS)), dim3(gdn::sum_threads<false>()), LS::bytes, s, pr);
-            // unrotated keys: their Gram matrix into the unrotated-key regions, the normalizer tile
+            // unrotated keys: their Gram matrix, the normalizer tile
             gdn::FrameParams<E> pu = p;
             pu.k = p.fkt;
-            pu.sum_mode = 2;
-            pu.PG = p.PGz;
-            pu.Gf = p.Gzf;
             if (e == hipSuccess)
-                e = launch((const void *)gdn::gdn_frame_summary_kernel<E, DK, DV, true, false>,
+                e = launch((const void *)gdn::gdn_frame_summary_kernel<E, DK, DV, true, false, true>,
                            dim3((unsigned)(units * p.NS)), dim3(gdn::sum_threads<false>()), LS::bytes, s, pu);
             return e;
         }
@@ -802,14 +807,9 @@ hipError_t launch_frame_fused32(const gdn::FrameParams<float> &p, hipStream_t s,
         case 2:
             return launch((const void *)gdn::gdn_frame_scan_kernel<E, DK, DV, true, BIDIR, true>,
                           dim3(gdn::xcd_blocks(BH, NJ)), dim3(64), 0, s, p);
-        default: {
-            hipError_t e = launch((const void *)gdn::gdn_frame_output_f32_fused_kernel<DK, DV>,
-                                  dim3(gdn::xcd_blocks(units, p.OB)), dim3(LO::WAVES * 64), LO::bytes, s, p);
-            if (e == hipSuccess)
-                e = launch((const void *)gdn::gdn_frame_project_f32_kernel<DV>,
-                           dim3((unsigned)(((size_t)p.F * p.N + 63) / 64), (unsigned)BH), dim3(256), LP::bytes, s, p);
-            return e;
-        }
+        default:
+            return launch((const void *)gdn::gdn_frame_output_fused32_kernel<DK, DV>, dim3(gdn::xcd_blocks(units, p.OB)),
+                          dim3(gdn::kFusedOutWaves32 * 64), LO::bytes, s, p);
         }
     };
     hipError_t er = hipSuccess;

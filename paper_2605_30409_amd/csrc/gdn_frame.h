@@ -91,11 +91,11 @@ template <class E> struct FrameParams {
     const int *rope_axis;        // [Dk/2]         its coordinate: 0 time, 1 latent row, else latent column
     float rms_eps, feat_scale;   // RMSNorm epsilon; key scale applied to the key features
     int lat_w, t0;               // tokens per latent row; time coordinate of frame 0
-    // the fused operator in fp32: its feature maps and gated readout in the
-    // workspace, and which summaries a summary launch stores
-    float *fqt, *fqh, *fkt, *fkh;  // [B][T][H][Dk]  q~, q^, k~, k^
-    float *ybuf;                 // [B][T][H][Dv]  SiLU(gate) o y
-    int sum_mode;                // 0 all; 1 all but the normalizer tile; 2 all but the A tiles
+    // the fused operator in fp32: its key features and rotation table in the
+    // workspace
+    float *fkt, *fkh;            // [B][T][H][Dk]  k~, k^
+    float *rope;                 // [F + max(latent rows, columns)][Dk/2][2]  cosine and sine (see gdn_frame_rope_kernel)
+    int no_z;                    // the summaries leave the normalizer tile out
 };
 
 // A fragment of ones: as the B operand, a 16-column tile whose every column is
@@ -248,9 +248,17 @@ template <int R> __device__ __forceinline__ float group_sum(float x) {
 constexpr int kSumCompute = 8, kSumLoaders = 4;
 template <bool FUSED> constexpr int sum_threads() { return (kSumCompute + (FUSED ? 4 : 0) + kSumLoaders) * 64; }
 
-template <class E, int DK, int DV, bool NORM, bool FUSED = false>
+// UNROT (the unrotated keys of the fused operator in fp32): the Gram matrix into
+// Gzf / PGz and the normalizer tile only.  All eight compute waves share the Gram
+// matrix and no values are copied.  Only the tiles on and above the diagonal are
+// formed where only they are kept (several splits); the waves of one SIMD (w and
+// w + 4) take row pairs whose shares above the diagonal add up to 6 or 4 of the 16
+// tile pairs that two such waves of the plain kernel carry (114 -> 60 us where the
+// plain kernel also formed the A tiles and dropped them).
+template <class E, int DK, int DV, bool NORM, bool FUSED = false, bool UNROT = false>
 __global__ __launch_bounds__(sum_threads<FUSED>()) void gdn_frame_summary_kernel(FrameParams<E> p) {
     static_assert(!FUSED || (NORM && sizeof(E) == 2), "the fused operator is normalized and bf16");
+    static_assert(!UNROT || (NORM && !FUSED), "the unrotated pass is normalized");
     using L = FrameSumLds<E, DK, DV, FUSED>;
     using TR = Tr<E>;
     using frag = typename TR::frag;
@@ -439,7 +447,7 @@ __global__ __launch_bounds__(sum_threads<FUSED>()) void gdn_frame_summary_kernel
                     __builtin_amdgcn_global_load_lds(
                         (const void *)(bb + (unsigned)min(l, rmax) * (unsigned)(4 * p.H)), GDN_SUM_DST(L::oB), 4, 0, 0);
                 }
-            } else {
+            } else if constexpr (!UNROT) {
                 const char *base = (const char *)(p.v + row0 * DV);
                 const unsigned rstride = (unsigned)(p.H * DV * ESZ);
 #pragma unroll
@@ -472,6 +480,76 @@ __global__ __launch_bounds__(sum_threads<FUSED>()) void gdn_frame_summary_kernel
     }
 
     // ---------------- compute waves ----------------
+    if constexpr (UNROT) {
+        constexpr int SH = kSumCompute / NP, CP = NCG / SH;           // column shares per row pair, tiles per share
+        const int kbw = w < 4 ? w % NP : NP - 1 - w % NP, c0 = CP * (w / NP);
+        const bool zw = c0 == 0;
+        f32x4 acc[2][CP], accz[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            accz[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < CP; ++j) acc[a][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        const frag ones = ones_frag<E>();
+        const int cmin = p.NS > 1 ? 2 * kbw : 0;                      // first column tile kept
+        const bool any = c0 + CP > cmin;
+        for (int i = 0; i < nb; ++i) {
+            lds_only_barrier();                                       // block i has landed
+            if (!any && !zw) continue;
+            const E *sK = (const E *)(slot(i) + L::oK);
+            const float *sB = (const float *)(slot(i) + L::oB);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                const f32x4 be0 = *(const f32x4 *)(sB + 32 * kb + 8 * lg), be1 = *(const f32x4 *)(sB + 32 * kb + 8 * lg + 4);
+                const int nvalid = t_hi - (t_lo + 64 * i + 32 * kb + 8 * lg);
+                float bt[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) bt[q] = q < nvalid ? (q < 4 ? be0[q] : be1[q - 4]) : 0.f;
+                frag fa[2];
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+                    fa[a] = scale_frag(tr_frag_gm<E, RK>(sK, 32 * kb, 32 * kbw, true, a, li, lg), bt);
+#pragma unroll
+                for (int j = 0; j < CP; ++j) {
+                    const int c = c0 + j;
+                    if (c < cmin) continue;
+                    const frag fb = tr_frag_gm<E, RK>(sK, 32 * kb, 32 * (c >> 1), true, c & 1, li, lg);
+#pragma unroll
+                    for (int a = 0; a < 2; ++a) acc[a][j] = TR::mma(fa[a], fb, acc[a][j]);
+                }
+                if (zw) {
+#pragma unroll
+                    for (int a = 0; a < 2; ++a) accz[a] = TR::mma(fa[a], ones, accz[a]);
+                }
+            }
+        }
+        const size_t fi = (size_t)bh * p.F + f;
+        if (p.NS == 1) {
+            const float ks = p.key_scale, k2 = ks * ks;
+#pragma unroll
+            for (int j = 0; j < CP; ++j)
+                TR::store8(p.Gzf + ((fi * NR + c0 + j) * KBN + kbw) * 512 + l * 8,
+                           TR::cat(TR::from_f32(acc[0][j] * k2), TR::from_f32(acc[1][j] * k2)));
+            if (zw) {
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+                    *(f32x4 *)(p.Af + ((fi * NR + 2 * kbw + a) * NJA + NCA) * 256 + l * 4) = accz[a] * ks;
+            }
+        } else {
+            float *dst = p.PGz + (fi * p.NS + s) * (size_t)NR * NCG * 256;
+            float *dz = p.PA + (fi * p.NS + s) * (size_t)NR * NJA * 256;
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+#pragma unroll
+                for (int j = 0; j < CP; ++j)
+                    if (c0 + j >= 2 * kbw + a)
+                        *(f32x4 *)(dst + ((size_t)((2 * kbw + a) * NCG + c0 + j) * 64 + l) * 4) = acc[a][j];
+                if (zw) *(f32x4 *)(dz + ((size_t)((2 * kbw + a) * NJA + NCA) * 64 + l) * 4) = accz[a];
+            }
+        }
+        return;
+    }
     const bool gw = w < 4;                                            // G waves (4..7: A waves)
     const bool zgw = FUSED && w >= 8;                                 // unrotated Gram waves (FUSED)
     const int wq = w & 3, kbw = wq % NP, c0 = wq / NP;                // row pair, column share
@@ -620,16 +698,14 @@ __global__ __launch_bounds__(sum_threads<FUSED>()) void gdn_frame_summary_kernel
                     *(f32x4 *)(p.Af + ((fi * NR + 2 * kbw + a) * NJA + NCA) * 256 + l * 4) = accz[a] * ks;
             }
         } else {
-            if (p.sum_mode != 2) {
 #pragma unroll
-                for (int j = 0; j < CPA; ++j) {
-                    const int jt = c0 * CPA + j;
+            for (int j = 0; j < CPA; ++j) {
+                const int jt = c0 * CPA + j;
 #pragma unroll
-                    for (int a = 0; a < 2; ++a)
-                        *(f32x4 *)(p.Af + ((fi * NR + 2 * kbw + a) * NJA + jt) * 256 + l * 4) = acc[a][j] * ks;
-                }
+                for (int a = 0; a < 2; ++a)
+                    *(f32x4 *)(p.Af + ((fi * NR + 2 * kbw + a) * NJA + jt) * 256 + l * 4) = acc[a][j] * ks;
             }
-            if (!FUSED && zw && p.sum_mode != 1) {
+            if (!FUSED && zw && !p.no_z) {
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
                     *(f32x4 *)(p.Af + ((fi * NR + 2 * kbw + a) * NJA + NCA) * 256 + l * 4) = accz[a] * ks;
@@ -640,15 +716,13 @@ __global__ __launch_bounds__(sum_threads<FUSED>()) void gdn_frame_summary_kernel
         // diagonal (column tile >= row tile) go to the partials
         const int NC = gram ? NCG : NJA;
         float *dst = (gw ? p.PG : zgw ? p.PGz : p.PA) + (fi * p.NS + s) * (size_t)NR * NC * 256;
-        if (gram || p.sum_mode != 2) {
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int j = 0; j < CPW; ++j)
-                    if (j < cpw && (!gram || c0 * cpw + j >= 2 * kbw + a))
-                        *(f32x4 *)(dst + ((size_t)((2 * kbw + a) * NC + c0 * cpw + j) * 64 + l) * 4) = acc[a][j];
-        }
-        if (zw && (FUSED || p.sum_mode != 1)) {
+            for (int j = 0; j < CPW; ++j)
+                if (j < cpw && (!gram || c0 * cpw + j >= 2 * kbw + a))
+                    *(f32x4 *)(dst + ((size_t)((2 * kbw + a) * NC + c0 * cpw + j) * 64 + l) * 4) = acc[a][j];
+        if (zw && (FUSED || !p.no_z)) {
             // the A partials' normalizer tile (FUSED: written by the unrotated Gram waves)
             float *dz = p.PA + (fi * p.NS + s) * (size_t)NR * NJA * 256;
 #pragma unroll
@@ -1231,191 +1305,239 @@ __global__ __launch_bounds__(kFusedOutWaves * 64) void gdn_frame_output_fused_ke
 // ---------------------------------------------------------------------------
 // The fused operator in fp32 (the paper's "ieee" precision mode, appendix "GDN
 // Kernel Details", "Precision modes"): every feature, product and readout in
-// fp32.  Phase A's feature maps are formed once per token by
-// gdn_frame_features_kernel into the workspace; the summaries then run as the
-// plain frame-wise summary kernel twice (rotated keys: G and A; unrotated
-// keys: the normalizer's Gram matrix and K~^T beta); the split reduction and
-// the scan are the fused variants; Phase C is gdn_frame_output_f32_fused_kernel
-// (numerator on q^, normalizer on q~, gate) and gdn_frame_project_f32_kernel
-// (the per-head projection).
+// fp32.  gdn_frame_rope_kernel tabulates the rotations; gdn_frame_kfeatures_kernel
+// forms the key features once per token into the workspace; the summaries run on
+// them as the plain frame-wise kernel (rotated keys: G and A) and its UNROT
+// variant (unrotated keys: the normalizer's Gram matrix and K~^T beta); the split
+// reduction and the scan are the fused variants; gdn_frame_output_fused32_kernel
+// forms the query features and ends in the projection.
 // ---------------------------------------------------------------------------
 
-// Features of every token row of q_raw and k_raw: with r(x) = gain o x /
-// sqrt(mean_i x_i^2 + rms_eps),
-//   q~ = ReLU(r_q(q)),  q^ = R q~,  k~ = feat_scale ReLU(r_k(k)),  k^ = R k~,
-// R rotating channel pair (2i, 2i + 1) by rope_freq[i] times the token's
-// coordinate on rope_axis[i] (0 time t0 + f, 1 latent row s / lat_w, else
-// latent column s % lat_w).  One lane per channel pair, Dk / 2 lanes per row
-// (the row's sum of squares reduced across them); the angle in fp64 and its
-// sine and cosine by the accurate fp64 routine, so that long time coordinates
-// cost no precision.
+// Rotation table: row f < F holds the cosine and sine of every channel pair at
+// the time coordinate t0 + f, row F + y at the latent row or column y (a pair
+// uses the rows of its own axis only).  The angle in fp64 and its sine and cosine
+// by the accurate fp64 routine, so that long time coordinates cost no precision.
+// They depend on neither head nor token beyond its coordinates: formed per token,
+// head and operand they took most of a 177 us kernel (3 frames of 3520 tokens, H
+// = 16); the table has some hundred rows.
 template <int DK>
-__global__ __launch_bounds__(256) void gdn_frame_features_kernel(FrameParams<float> p) {
-    constexpr int P = DK / 2;                                   // lanes per row
-    const size_t nrow = (size_t)p.B * p.F * p.N * p.H;           // rows per tensor
-    const int l = threadIdx.x & 63;
-    const size_t r = ((size_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / P) + l / P;
-    if (r >= 2 * nrow) return;
-    const bool isk = r >= nrow;
-    const size_t row = isk ? r - nrow : r;                       // (b T + t) H + h
-    const int h = (int)(row % p.H);
-    const int t = (int)((row / p.H) % ((size_t)p.F * p.N));
-    const int f = t / p.N, sidx = t - f * p.N;
-    const int i = l % P;
-    const float2 x = *(const float2 *)((isk ? p.k : p.q) + row * DK + 2 * i);
-    float ss = x.x * x.x + x.y * x.y;
-#pragma unroll
-    for (int o = P / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
-    const float inv = 1.f / sqrtf(ss * (1.f / DK) + p.rms_eps);
-    const float *gain = (isk ? p.gain_k : p.gain_q) + (size_t)h * DK + 2 * i;
-    const float sc = isk ? p.feat_scale : 1.f;
-    const float x0 = sc * fmaxf(gain[0] * x.x * inv, 0.f), x1 = sc * fmaxf(gain[1] * x.y * inv, 0.f);
-    const int ax = p.rope_axis[i];
-    const int yc = sidx / p.lat_w;
-    const double coord = ax == 0 ? (double)(p.t0 + f) : ax == 1 ? (double)yc : (double)(sidx - yc * p.lat_w);
+__global__ __launch_bounds__(256) void gdn_frame_rope_kernel(FrameParams<float> p, int rows) {
+    constexpr int P = DK / 2;
+    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const int r = (int)(idx / P), i = (int)(idx % P);
+    if (r >= rows) return;
+    const double coord = r < p.F ? (double)(p.t0 + r) : (double)(r - p.F);
     double sn, cs;
     sincos((double)p.rope_freq[i] * coord, &sn, &cs);
-    const float s1 = (float)sn, c1 = (float)cs;
-    float *ft = (isk ? p.fkt : p.fqt) + row * DK + 2 * i, *fh = (isk ? p.fkh : p.fqh) + row * DK + 2 * i;
-    *(float2 *)ft = make_float2(x0, x1);
-    *(float2 *)fh = make_float2(x0 * c1 - x1 * s1, x0 * s1 + x1 * c1);
+    *(float2 *)(p.rope + 2 * ((size_t)r * P + i)) = make_float2((float)cs, (float)sn);
 }
 
-// Phase C numerator, normalizer and gate in fp32: as gdn_frame_output_kernel
-// with the normalizer (one 16-token tile per wave at a time, H_f of the
-// (frame, head) in LDS), with the numerator tiles on q^, the normalizer tile
-// on q~, and y = SiLU(gate) o numerator / (z . q~ + eps) written to ybuf.
+// Key features of every token row: with r(x) = gain o x / sqrt(mean_i x_i^2 +
+// rms_eps),  k~ = feat_scale ReLU(r(k)),  k^ = R k~,  R rotating channel pair
+// (2i, 2i + 1) by rope_freq[i] times the token's coordinate on rope_axis[i] (0
+// time t0 + f, 1 latent row s / lat_w, else latent column s % lat_w).  Two
+// channel pairs (16 bytes) per lane, Dk / 4 lanes per row (the row's sum of
+// squares reduced across them).  Bound by HBM: one read and two writes of the
+// key tensor, 260 MB in 43 us (3 frames of 3520 tokens, H = 16).
+template <int DK>
+__global__ __launch_bounds__(256) void gdn_frame_kfeatures_kernel(FrameParams<float> p) {
+    constexpr int LR = DK / 4;                                  // lanes per row
+    const size_t nrow = (size_t)p.B * p.F * p.N * p.H;
+    const int l = threadIdx.x & 63;
+    const size_t row = ((size_t)blockIdx.x * 256 + threadIdx.x) / LR;   // (b T + t) H + h
+    if (row >= nrow) return;
+    const int h = (int)(row % p.H);
+    const int t = (int)((row / p.H) % ((size_t)p.F * p.N));
+    const int f = t / p.N, sidx = t - f * p.N, yc = sidx / p.lat_w, xc = sidx - yc * p.lat_w;
+    const int i = 2 * (l % LR);                                 // first channel pair
+    const f32x4 x = *(const f32x4 *)(p.k + row * DK + 2 * i);
+    float ss = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
+#pragma unroll
+    for (int o = LR / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
+    const float inv = 1.f / sqrtf(ss * (1.f / DK) + p.rms_eps);
+    const f32x4 gain = *(const f32x4 *)(p.gain_k + (size_t)h * DK + 2 * i);
+    f32x4 ft, fh;
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        const int ax = p.rope_axis[i + d];
+        const int r = ax == 0 ? f : p.F + (ax == 1 ? yc : xc);
+        const float2 cs = *(const float2 *)(p.rope + 2 * ((size_t)r * (DK / 2) + i + d));
+        const float x0 = p.feat_scale * fmaxf(gain[2 * d] * x[2 * d] * inv, 0.f),
+                    x1 = p.feat_scale * fmaxf(gain[2 * d + 1] * x[2 * d + 1] * inv, 0.f);
+        ft[2 * d] = x0;
+        ft[2 * d + 1] = x1;
+        fh[2 * d] = x0 * cs.x - x1 * cs.y;
+        fh[2 * d + 1] = x0 * cs.y + x1 * cs.x;
+    }
+    *(f32x4 *)(p.fkt + row * DK + 2 * i) = ft;
+    *(f32x4 *)(p.fkh + row * DK + 2 * i) = fh;
+}
+
+// Phase C in fp32: gdn_frame_output_fused_kernel's stages and channel order with
+// fp32 operands (16x16x4 MFMA) and the rotation table.  H_f and W_o take 137 KB of
+// LDS as fragments (the halves of a lane's eight values in planes of 16 bytes per
+// lane), so one workgroup of 8 waves runs per CU.  Bound by the matrix cores: 544
+// MFMAs of 32 cycles per 16-token tile (75 us for 3 frames of 3520 tokens, H =
+// 16; measured 137, with 4 waves 158).  As two kernels with the gated readout, the
+// query features and their rotation through HBM it took 116 + 161 us beside half
+// of the 177 us features.
+constexpr int kFusedOutWaves32 = 8;
+
+template <int DK, int DV> struct FusedOut32Lds {
+    static constexpr int NJ = DV / 16 + 1;
+    static constexpr size_t oW = (size_t)4 * DK * 16 * NJ;      // after H_f: W_o fragments
+    static constexpr size_t oP = oW + (size_t)4 * DV * DV;      // gain_q[DK], rope_axis[DK / 2]
+    static constexpr size_t bytes = oP + (size_t)4 * (DK + DK / 2);
+};
+
 template <int DK, int DV>
-__global__ __launch_bounds__(64 * frame_out_waves<true>()) void gdn_frame_output_f32_fused_kernel(
-    FrameParams<float> p) {
-    using E = float;
-    using TR = Tr<E>;
-    using frag = typename TR::frag;
-    using LO = FrameOutLds<E, DK, DV, true>;
-    constexpr int KB = DK / 32, NV = DV / 16, NJ = LO::NJ;
-    constexpr int HV = NJ * 16 * DK * (int)sizeof(E) / 16;    // 16-byte vectors of H_f
+__global__ __launch_bounds__(kFusedOutWaves32 * 64) void gdn_frame_output_fused32_kernel(FrameParams<float> p) {
+    using TR = Tr<float>;
+    using frag = TR::frag;
+    using LO = FusedOut32Lds<DK, DV>;
+    constexpr int KB = DK / 32, NV = DV / 16, NJ = LO::NJ, KBV = DV / 32;
+    constexpr int NTH = kFusedOutWaves32 * 64;
     extern __shared__ __align__(16) unsigned char smem[];
     int unit, blk;
     xcd_unit(blockIdx.x, p.OB, unit, blk);
     if (unit >= p.F * p.B * p.H) return;
     const int bh = unit / p.F, f = unit - bh * p.F;
     const int b = bh / p.H, h = bh - b * p.H;
-    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, li = l & 15, lg = l >> 4;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, li = l & 15, lg = l >> 4;
     const size_t fi = (size_t)bh * p.F + f;
+    // staging: 16-byte piece (fragment, half, lane), all of a thread's loads in flight
     {
-        constexpr int NTH = 64 * LO::WAVES, HIT = (HV + NTH - 1) / NTH;
-        const u32x4 *src = (const u32x4 *)(p.Hf + fi * (size_t)NJ * 16 * DK);
-        u32x4 hv[HIT];
+        constexpr int HV = NJ * KB * 128, HIT = (HV + NTH - 1) / NTH, WV = NV * KBV * 128, WIT = WV / NTH;
+        static_assert(WV % NTH == 0, "whole rounds of W_o pieces");
+        const float *src = p.Hf + fi * (size_t)NJ * 16 * DK;
+        f32x4 hv[HIT], wv[WIT];
+#pragma unroll
+        for (int it = 0; it < HIT; ++it) {
+            const int d = min(tid + NTH * it, HV - 1);
+            const int fr = d >> 7, half = (d >> 6) & 1, ll = d & 63, jo = fr / KB, kb = fr - jo * KB;
+            int sf = fr, sl = ll;
+            if (jo < NV) {
+                const int c = fused_out_chan(jo, ll & 15);
+                sf = (c >> 4) * KB + kb;
+                sl = (c & 15) + (ll & 48);
+            }
+            hv[it] = *(const f32x4 *)(src + (size_t)sf * 512 + sl * 8 + 4 * half);
+        }
+#pragma unroll
+        for (int it = 0; it < WIT; ++it) {
+            const int d = tid + NTH * it;
+            const int fr = d >> 7, half = (d >> 6) & 1, ll = d & 63, jo = fr / KBV, kb = fr - jo * KBV;
+            wv[it] = *(const f32x4 *)(p.w_o + ((size_t)h * DV + fused_out_chan(jo, ll & 15)) * DV + 32 * kb +
+                                      8 * (ll >> 4) + 4 * half);
+        }
 #pragma unroll
         for (int it = 0; it < HIT; ++it)
-            if (HV % NTH == 0 || tid + NTH * it < HV) hv[it] = src[tid + NTH * it];
+            if (HV % NTH == 0 || tid + NTH * it < HV) ((f32x4 *)smem)[tid + NTH * it] = hv[it];
 #pragma unroll
-        for (int it = 0; it < HIT; ++it)
-            if (HV % NTH == 0 || tid + NTH * it < HV) ((u32x4 *)smem)[tid + NTH * it] = hv[it];
+        for (int it = 0; it < WIT; ++it) ((f32x4 *)(smem + LO::oW))[tid + NTH * it] = wv[it];
+        float *cp = (float *)(smem + LO::oP);
+        for (int j = tid; j < DK + DK / 2; j += NTH) {
+            if (j < DK)
+                cp[j] = p.gain_q[h * DK + j];
+            else
+                ((int *)cp)[j] = p.rope_axis[j - DK];
+        }
     }
     const size_t T = (size_t)p.F * p.N;
     const int ntf = (p.N + 15) / 16;
     const int tile_lo = blk * p.OTPW, tile_hi = min(ntf, tile_lo + p.OTPW);
     const size_t row_f = (size_t)b * T + (size_t)f * p.N;
-    // query features of tile i (rotated and unrotated); rows past the frame
-    // read its last token
-    auto load_q = [&](int i, frag (&qh)[KB], frag (&qt)[KB]) {
-        const int n = min(16 * i + li, p.N - 1);
-        const size_t o = ((row_f + n) * p.H + h) * DK;
+    const float *cgain = (const float *)(smem + LO::oP);
+    const int *caxis = (const int *)(cgain + DK);
+    auto row_of = [&](int tile) { return (row_f + min(16 * tile + li, p.N - 1)) * p.H + h; };
+    // raw query rows of tile i; rows past the frame read its last token
+    auto load_q = [&](int i, frag (&qf)[KB]) {
+        const float *qrow = p.q + row_of(i) * DK;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) qf[kb] = load_frag<float>(qrow + 32 * kb, lg);
+    };
+    auto compute = [&](int tile, const frag (&x)[KB]) {
+        // an offset the compiler cannot see through: the fragments are read from
+        // LDS where they are used rather than held in registers across tiles
+        int lo = 0;
+        asm volatile("" : "+v"(lo));
+        const f32x4 *tH = (const f32x4 *)smem + l + lo, *tW = (const f32x4 *)(smem + LO::oW) + l + lo;
+        auto hfrag = [&](int jo, int kb) { return TR::cat(tH[(jo * KB + kb) * 128], tH[(jo * KB + kb) * 128 + 64]); };
+        auto wfrag = [&](int jo, int kb) { return TR::cat(tW[(jo * KBV + kb) * 128], tW[(jo * KBV + kb) * 128 + 64]); };
+        const float *grow = p.gate + row_of(tile) * DV + 8 * lg;
+        frag gt[KBV];
+#pragma unroll
+        for (int kb = 0; kb < KBV; ++kb) gt[kb] = TR::load8(grow + 32 * kb);
+        const int n = min(16 * tile + li, p.N - 1), yc = n / p.lat_w, xc = n - yc * p.lat_w;
+        float ss = 0.f;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) ss += x[kb][q] * x[kb][q];
+        ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        const float inv = 1.f / sqrtf(ss * (1.f / DK) + p.rms_eps);
+        frag qt[KB], qh[KB];
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
-            qh[kb] = load_frag<E>(p.fqh + o + 32 * kb, lg);
-            qt[kb] = load_frag<E>(p.fqt + o + 32 * kb, lg);
+            const int ch = 32 * kb + 8 * lg;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int ax = caxis[ch / 2 + d], r = ax == 0 ? f : p.F + (ax == 1 ? yc : xc);
+                const float2 cs = *(const float2 *)(p.rope + 2 * ((size_t)r * (DK / 2) + ch / 2 + d));
+                const float x0 = fmaxf(cgain[ch + 2 * d] * x[kb][2 * d] * inv, 0.f),
+                            x1 = fmaxf(cgain[ch + 2 * d + 1] * x[kb][2 * d + 1] * inv, 0.f);
+                qt[kb][2 * d] = x0;
+                qt[kb][2 * d + 1] = x1;
+                qh[kb][2 * d] = x0 * cs.x - x1 * cs.y;
+                qh[kb][2 * d + 1] = x0 * cs.y + x1 * cs.x;
+            }
+        }
+        f32x4 dz = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) dz = TR::mma(hfrag(NV, kb), qt[kb], dz);
+        const float invd = 1.f / (dz[0] + p.eps);
+        frag yb[KBV];
+#pragma unroll
+        for (int kv = 0; kv < KBV; ++kv) {
+            f32x4 acc[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // the two tiles' chains interleaved
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) acc[e] = TR::mma(hfrag(2 * kv + e, kb), qh[kb], acc[e]);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const float g = gt[kv][q];
+                yb[kv][q] = g / (1.f + expf(-g)) * (acc[q >> 2][q & 3] * invd);
+            }
+        }
+        const bool live = tile < tile_hi && 16 * tile + li < p.N;
+        float *orow = p.out + ((row_f + 16 * tile + li) * p.H + h) * DV + 8 * lg;
+#pragma unroll
+        for (int kv = 0; kv < KBV; ++kv) {
+            f32x4 o[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kb = 0; kb < KBV; ++kb)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) o[e] = TR::mma(wfrag(2 * kv + e, kb), yb[kb], o[e]);
+            if (live) TR::store8(orow + 32 * kv, TR::cat(o[0], o[1]));
         }
     };
-    const E *sH = (const E *)smem + l * 8;
-    E *sO = (E *)(smem + LO::oO) + w * 16 * LO::LDO;
-    constexpr int RV = DV / 4;                                 // float4 per row
-    auto tile_product = [&](int jo, const frag (&qf)[KB]) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) acc = TR::mma(TR::load8(sH + (jo * KB + kb) * 512), qf[kb], acc);
-        return acc;
-    };
-    auto compute = [&](int tile, const frag (&qh)[KB], const frag (&qt)[KB]) {
-        f32x4 acc[NV];
-#pragma unroll
-        for (int jo = 0; jo < NV; ++jo) acc[jo] = tile_product(jo, qh);
-        const float inv = 1.f / (tile_product(NV, qt)[0] + p.eps);
-        // lane (li, lg) holds columns 16 jo + 4 lg + q of token li
-        const int n = min(16 * tile + li, p.N - 1);
-        const float *grow = p.gate + ((row_f + n) * p.H + h) * DV;
-#pragma unroll
-        for (int jo = 0; jo < NV; ++jo) {
-            const f32x4 g = *(const f32x4 *)(grow + 16 * jo + 4 * lg);
-            f32x4 y;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) y[q] = g[q] / (1.f + expf(-g[q])) * (acc[jo][q] * inv);
-            *(f32x4 *)(sO + li * LO::LDO + 16 * jo + 4 * lg) = y;
-        }
-#pragma unroll
-        for (int pass = 0; pass < 16 * RV / 64; ++pass) {
-            const int r = pass * (64 / RV) + l / RV, c = (l % RV) * 4;
-            const f32x4 val = *(const f32x4 *)(sO + r * LO::LDO + c);
-            const int nn = 16 * tile + r;
-            if (tile < tile_hi && nn < p.N) *(f32x4 *)(p.ybuf + ((row_f + nn) * p.H + h) * DV + c) = val;
-        }
-    };
-    auto clampi = [&](int i) { return min(i, tile_hi - 1); };
-    frag ha[KB], ta[KB], hb[KB], tb[KB];
+    frag qa[KB];
     const int i0 = tile_lo + w;
-    load_q(clampi(i0), ha, ta);
-    lds_barrier();
-    constexpr int SW = LO::WAVES;
-    for (int i = i0; i < tile_hi; i += 2 * SW) {
-        load_q(clampi(i + SW), hb, tb);
-        compute(i, ha, ta);
-        if (i + SW >= tile_hi) break;
-        load_q(clampi(i + 2 * SW), ha, ta);
-        compute(i + SW, hb, tb);
-    }
-}
-
-// The per-head projection in fp32: out_n = W_o[h] ybuf_n.  Workgroup (run of 64
-// tokens, b h): W_o[h] and the run's rows of ybuf staged in LDS with row
-// stride DV + 4 (the 16 rows x 4 k slots an operand read touches fall in 64
-// distinct banks); wave w takes tokens 16 w .. 16 w + 15 of the run and every
-// 16-channel output tile on 16x16x4 fp32 MFMA, lane (li, lg) supplying
-// W_o[16 it + li][4 kk + lg] and ybuf[token li][4 kk + lg]; the accumulator
-// lane (li, lg) then holds channels 16 it + 4 lg .. + 3 of token li.
-template <int DV> struct ProjectLds {
-    static constexpr int LD = DV + 4;
-    static constexpr size_t bytes = (size_t)4 * (DV + 64) * LD;
-};
-
-template <int DV>
-__global__ __launch_bounds__(256) void gdn_frame_project_f32_kernel(FrameParams<float> p) {
-    constexpr int LD = ProjectLds<DV>::LD, RV = DV / 4;
-    extern __shared__ __align__(16) unsigned char smem[];
-    float *sW = (float *)smem, *sY = sW + DV * LD;
-    const size_t T = (size_t)p.F * p.N;
-    const int bh = blockIdx.y, b = bh / p.H, h = bh - b * p.H;
-    const int t0 = blockIdx.x * 64;
-    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, li = l & 15, lg = l >> 4;
-    for (int idx = tid; idx < DV * RV; idx += 256) {
-        const int r = idx / RV, c = idx - r * RV;
-        *(f32x4 *)(sW + r * LD + 4 * c) = *(const f32x4 *)(p.w_o + ((size_t)h * DV + r) * DV + 4 * c);
-    }
-    for (int idx = tid; idx < 64 * RV; idx += 256) {
-        const int r = idx / RV, c = idx - r * RV;
-        const size_t t = min((size_t)(t0 + r), T - 1);
-        *(f32x4 *)(sY + r * LD + 4 * c) = *(const f32x4 *)(p.ybuf + (((size_t)b * T + t) * p.H + h) * DV + 4 * c);
-    }
-    __syncthreads();
-    const float *yl = sY + (16 * w + li) * LD + lg;
-    const size_t tok = (size_t)t0 + 16 * w + li;
-#pragma unroll 2
-    for (int it = 0; it < DV / 16; ++it) {
-        const float *wl = sW + (16 * it + li) * LD + lg;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    load_q(min(i0, tile_hi - 1), qa);
+    lds_barrier();                                // staging complete
+    for (int i = i0; i < tile_hi; i += kFusedOutWaves32) {
+        frag qc[KB];
 #pragma unroll
-        for (int kk = 0; kk < DV / 4; ++kk) acc = mma_f32_k4(wl[4 * kk], yl[4 * kk], acc);
-        if (tok < T) *(f32x4 *)(p.out + (((size_t)b * T + tok) * p.H + h) * DV + 16 * it + 4 * lg) = acc;
+        for (int kb = 0; kb < KB; ++kb) qc[kb] = qa[kb];
+        load_q(min(i + kFusedOutWaves32, tile_hi - 1), qa);
+        compute(i, qc);
     }
 }
 
