@@ -46,9 +46,8 @@ PEAK_F32_TFLOPS = 157.3      # MI355X fp32 matrix
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E
 # stage name (as the library reports stages) -> kernel
 KERNELS = {"wy": "gdn_wy_kernel", "group_transfer": "gdn_chunkscan_kernel<SCAN_TRANS>",
-           "group_scan": "gdn_groupscan_kernel", "chunk_states": "gdn_chunkscan_kernel<SCAN_STATES>",
-           "output": "gdn_output_kernel"}
-KERNELS_FUSED = dict(KERNELS, chunk_states="gdn_chunkscan_kernel<SCAN_STATES, output fused>")
+           "group_scan": "gdn_groupscan_kernel",
+           "chunk_states": "gdn_chunkscan_kernel<SCAN_STATES, output fused>"}
 EXTRA_WORKLOADS = (0, 2, 3, 4)
 # committed counter summaries of the token path, per workload
 TRAFFIC_SUMMARY = {1: "traffic_frame1280x704.json", 2: "traffic_stream3x1280x704.json",
@@ -72,29 +71,24 @@ def path_counts(B, T, H, Dk, Dv, C=64, esz=2):
 def workspace_traffic(B, T, H, Dk, Dv, G, C=64, esz=2):
     """Workspace bytes each stage writes and reads (every byte once).  The WY
     kernel writes the gates (a record of the per-token key decay factors in fp32
-    with g_C; on the fp32 path also g), -W and U~t; the scans read the keys from
-    the input.  On the bf16 path the output is fused into the scan: the WY kernel
-    also writes the decay-scaled queries and the masked decayed Q K^T tile of
-    every chunk (row fragments the scan's output waves read) and the scan
-    writes no per-chunk state."""
+    with g_C), -W and U~t, and the decay-scaled queries and the masked decayed
+    Q K^T tile of every chunk (row fragments the scan's output waves read); the
+    scans read the keys from the input."""
     NC = -(-T // C)
     NG = -(-NC // G)
     nch = B * H * NC
-    fused = esz == 2
     ngr = B * H * NG if NG > 1 else 0
-    gates = nch * ((0 if fused else C * 8) + (C + 4) * 4)
+    gates = nch * (C + 4) * 4                              # key scales, g_C
     fac = nch * C * (Dk + Dv) * esz                        # -W, U~t
-    scan_gates = nch * (C + 4) * 4                         # key scales, g_C
-    qp = nch * C * (Dk + C) * esz if fused else 0          # scaled Q, masked P
+    qp = nch * C * (Dk + C) * esz                          # scaled Q, masked P
     grp = ngr * (Dk * Dk * esz + Dv * Dk * 4 + 8)          # N, Psi^T, log Gamma
     hg = ngr * Dv * Dk * 4                                 # group entry states
-    hs_us = 0 if fused else nch * Dv * (Dk + C) * esz      # per-chunk state and pseudo-values
     zero = {"written": 0, "read": 0}
     return {"wy": {"written": gates + fac + qp, "read": 0},
-            "group_transfer": {"written": grp, "read": fac + scan_gates} if ngr else zero,
+            "group_transfer": {"written": grp, "read": fac + gates} if ngr else zero,
             "group_scan": {"written": hg, "read": grp} if ngr else zero,
-            "chunk_states": {"written": hs_us, "read": fac + scan_gates + hg + qp},
-            "output": zero if fused else {"written": 0, "read": hs_us + nch * C * 8}}
+            "chunk_states": {"written": 0, "read": fac + gates + hg + qp},
+            "output": zero}
 
 
 def pct(xs, p):
@@ -242,7 +236,6 @@ def run_extra_workload(idx, gdn, torch, dev, stream, reps):
     torch.cuda.synchronize()
     names = {k: v for k, v in zip(gdn.STAGE_NAMES, stage) if v > 0}
     G = gdn.gdn_scan_group_size(B, H, T, Dk, Dv, is_bf16=esz == 2)
-    fused = esz == 2
     flops, io = path_counts(B, T, H, Dk, Dv, esz=esz)
     wst = workspace_traffic(B, T, H, Dk, Dv, G, esz=esz)
     ws_bytes = sum(v["written"] + v["read"] for v in wst.values())
@@ -254,9 +247,9 @@ def run_extra_workload(idx, gdn, torch, dev, stream, reps):
            "mfma_frac": round(flops / med / 1e12 / peak, 5), "peak_tflops": peak,
            "hbm_frac_io": round(io / med / 1e9 / PEAK_HBM_GBS, 4),
            "algorithmic_bytes": io, "algorithmic_flops": flops,
-           "scan_group": G, "output_fused": fused,
+           "scan_group": G, "output_fused": True,
            "stage_ms": {k: round(v, 5) for k, v in names.items()},
-           "dominant_kernel": (KERNELS_FUSED if fused else KERNELS).get(dom, dom),
+           "dominant_kernel": KERNELS.get(dom, dom),
            "workspace_bytes": ws_bytes,
            "workspace_gbs": round(ws_bytes / med / 1e9, 1)}
     del calls, out, st, ws
@@ -622,14 +615,13 @@ def main():
 
     G = gdn.gdn_scan_group_size(B, H, T, Dk, Dv, C, is_bf16=bf16)
     NG = -(-(-(-T // C)) // G)
-    fused = bf16
     esz = 2 if bf16 else 4
     flops, io = path_counts(B, T, H, Dk, Dv, C, esz=esz)
     sec = ms_per_step / 1e3
     tflops = flops / sec / 1e12
     peak = PEAK_BF16_TFLOPS if bf16 else PEAK_F32_TFLOPS
     traffic = load_traffic(TRAFFIC_SUMMARY.get(widx, "none"))
-    roofline = token_roofline(flops, io, names, KERNELS_FUSED if fused else KERNELS, traffic, peak)
+    roofline = token_roofline(flops, io, names, KERNELS, traffic, peak)
 
     rec = {
         "metric": METRIC if widx == WORKLOAD else f"GDN fwd tokens/sec and TFLOP/s, workload {w.name}",
@@ -649,7 +641,7 @@ def main():
                                + (f" (a step is one call of the {w.calls}-call chain, state threaded)"
                                   if w.calls > 1 else ""),
                    "B": B, "T": T, "H": H, "Dk": Dk, "Dv": Dv, "chunk": C,
-                   "scan_group": G, "scan_groups": NG, "output_fused": fused},
+                   "scan_group": G, "scan_groups": NG, "output_fused": True},
         "step_ms": stats(per_step),
         "tflops": round(tflops, 2),
         "mfma_frac": round(tflops / peak, 4),

@@ -134,9 +134,8 @@ size_t gdn_workspace_bytes_ex(int B, int H, int T, int Dk, int Dv, int chunk, in
 /*
  * Host-only consistency check of the workspace layout (no HIP call): for the
  * path a call with these arguments takes, every region of the workspace
- * (cumulative log decays, per-chunk gate records of key decay factors and
- * chunk decay, -W, U~t, per-chunk states or fused-output operands,
- * pseudo-values, and the grouped scan's transfers,
+ * (per-chunk gate records of key decay factors and chunk decay, -W, U~t, the
+ * output's scaled queries and masked scores, and the grouped scan's transfers,
  * offsets, log decays and entry states) starts 256-byte aligned and spans at
  * least the highest byte the kernels index in it (their index expressions at
  * the largest chunk and group index).  Returns GDN_OK, the 1-based number of
@@ -186,8 +185,9 @@ int gdn_chunk_forward_ex(const void *q, const void *k, const void *v,
  * previous stages' results), then synchronizes the stream and writes the mean
  * duration of one launch of each stage in milliseconds to stage_ms[0..4]
  * (host memory): [0] WY transform, [1] group transfer maps, [2] scan over
- * groups, [3] chunk states, [4] output.  Stages that do not run for this
- * shape (1 and 2 with a single scan group) report 0.  state_in ==
+ * groups, [3] chunk states and output, [4] always 0 (stage 3 forms the
+ * output).  Stages that do not run for this shape (1 and 2 with a single scan
+ * group) report 0; long calls are timed in one pass over their chunks.  state_in ==
  * state_out is rejected with GDN_ERR_ALIAS.  The outputs are those of one
  * ordinary call.  Creates and destroys its own events.
  */

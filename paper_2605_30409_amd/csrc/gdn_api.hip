@@ -55,10 +55,11 @@ WsLayout ws_layout(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
     L.gf = off;   off = align256(off + nch * kGateRec * 4);
     L.W = off;    off = align256(off + nch * kChunk * Dk * esz);
     L.Ut = off;   off = align256(off + nch * Dv * kChunk * esz);
-    // On the bf16 path these regions hold the chunk's decay-scaled queries
-    // (C x Dk) and masked scores (C x C) instead of the per-chunk state (Dv x Dk)
-    // and pseudo-values (Dv x C).  (With several groups they keep the larger
-    // sizes: a caller's workspace is sized the same as ever.)
+    // These regions hold the chunk's decay-scaled queries (C x Dk) and masked
+    // scores (C x C).  In fp32 and with several groups they keep the sizes of the
+    // per-chunk state (Dv x Dk) and pseudo-values (Dv x C) that an output kernel
+    // of its own once read there, and g its place: a caller's workspace is sized
+    // the same as ever.
     const bool fused = esz == 2 && NG == 1;
     L.Hs = off;   off = align256(off + nch * (fused ? kChunk : Dv) * Dk * esz);
     L.Us = off;   off = align256(off + nch * (fused ? kChunk : Dv) * kChunk * esz);
@@ -83,26 +84,18 @@ WsNeeds ws_needs(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
     const size_t NC = (size_t)num_chunks(T), NG = (NC + G - 1) / G;
     const size_t cmax = (size_t)B * H * NC - 1;             // last chunk record
     const size_t gmax = (size_t)B * H * NG - 1;             // last group record
-    const bool fused = esz == 2;  // the output is fused into the scan
     const size_t KB = (size_t)Dk / 32, NJ = (size_t)Dv / 16;
     WsNeeds n{};
-    // WY kernel: g[cidx * 64 + l], gf[cidx * 68 + l] and the fp64 g_C at
-    // gf + cidx * 68 + 64 (the scan copies gf[cidx * 68 + 4 l .. + 3], l < 17)
-    n.g = (cmax * kChunk + 63 + 1) * 8;
+    // WY kernel: gf[cidx * 68 + l] and the fp64 g_C at gf + cidx * 68 + 64 (the
+    // scan copies gf[cidx * 68 + 4 l .. + 3], l < 17)
     n.gf = (cmax * kGateRec + kGateRec) * 4;
     // -W fragment ((wv * 4 + st) * 2 + kb) * 512 + l * 8, 8 elements
     n.W = (cmax * kChunk * Dk + ((((size_t)Dk / 64 - 1) * 4 + 3) * 2 + 1) * 512 + 63 * 8 + 8) * esz;
     // U~t quad (4 jt + st) * 256 + l * 4, 4 elements
     n.Ut = (cmax * Dv * kChunk + (4 * (NJ - 1) + 3) * 256 + 63 * 4 + 4) * esz;
-    if (fused) {
-        // WY: Qf (rt * KB + kb) * 512 + l * 8 and Pf (rt * 2 + m) * 512 + l * 8
-        n.Hs = (cmax * kChunk * Dk + (3 * KB + KB - 1) * 512 + 63 * 8 + 8) * esz;
-        n.Us = (cmax * kChunk * kChunk + (3 * 2 + 1) * 512 + 63 * 8 + 8) * esz;
-    } else {
-        // chunk states: Hs[(column) * Dk + 32 kb + 8 lg], Us[(column) * 64 + 32 + 8 lg]
-        n.Hs = (cmax * Dv * Dk + (size_t)(Dv - 1) * Dk + 32 * (KB - 1) + 24 + 8) * esz;
-        n.Us = (cmax * Dv * kChunk + (size_t)(Dv - 1) * kChunk + 32 + 24 + 8) * esz;
-    }
+    // WY: Qf (rt * KB + kb) * 512 + l * 8 and Pf (rt * 2 + m) * 512 + l * 8
+    n.Hs = (cmax * kChunk * Dk + (3 * KB + KB - 1) * 512 + 63 * 8 + 8) * esz;
+    n.Us = (cmax * kChunk * kChunk + (3 * 2 + 1) * 512 + 63 * 8 + 8) * esz;
     if (NG > 1) {
         // group transfer: N fragments ((v * 4 + t) * (Dk / 32) + kb) * 512 + l * 8,
         // Psi^T[(gidx * Dv + column) * Dk + row], log Gamma[gidx]; group scan: H^T like Psi^T
@@ -183,16 +176,11 @@ gdn::Params<E> make_params(const void *q, const void *k, const void *v, const fl
     p.NG = (p.NC + G - 1) / G;
     const WsLayout L = ws_layout(B, H, T, Dk, Dv, sizeof(E), G);
     unsigned char *base = (unsigned char *)ws;
-    p.g = (double *)(base + L.g);
     p.gf = (float *)(base + L.gf);
     p.W = (E *)(base + L.W);
     p.Ut = (E *)(base + L.Ut);
-    p.Hs = (E *)(base + L.Hs);
-    p.Us = (E *)(base + L.Us);
-    // The output is fused into the scan on the bf16 path; its Q and P fragments
-    // live in the (unused) Hs and Us regions.
-    p.Qf = p.Hs;
-    p.Pf = p.Us;
+    p.Qf = (E *)(base + L.Hs);
+    p.Pf = (E *)(base + L.Us);
     p.Nf = (E *)(base + L.Nf);
     p.PsiT = (float *)(base + L.PsiT);
     p.lgam = (double *)(base + L.lgam);
@@ -210,15 +198,7 @@ hipError_t launch(const void *fn, dim3 grid, dim3 block, size_t lds, hipStream_t
     return hipLaunchKernel(fn, grid, block, args, lds, s);
 }
 
-// The fp32 path's output kernel (nullptr for bf16, whose scan forms the output).
-template <class E, int DK, int DV> const void *output_fn() {
-    if constexpr (sizeof(E) == 4)
-        return (const void *)gdn::gdn_output_kernel<E, DK, DV>;
-    else
-        return nullptr;
-}
-
-constexpr int kStages = 5;  // WY transform, group transfers, group scan, chunk states, output
+constexpr int kStages = 5;  // WY transform, group transfers, group scan, chunk states with output; none (the output's once)
 
 // Stage timing (measurement aid): every stage that launches is enqueued `reps`
 // times back to back between the events ev[2 s] and ev[2 s + 1].
@@ -230,7 +210,7 @@ struct StageTiming {
 
 template <class E, int DK, int DV>
 hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) {
-    constexpr int NOW = sizeof(E) == 2 ? 4 : 0;  // output waves: bf16 fuses the output into the scan
+    constexpr int NOW = 4;                       // output waves
     // Two column tiles per workgroup once one each would be more workgroups than
     // CUs: the pair reads the chunk operands once, and a second round of
     // workgroups or a shared CU costs more than the longer step (320 tiles of the
@@ -249,20 +229,17 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     const size_t lds1 = gdn::WyLds<E, DK, DV>::bytes;
-    const size_t lds3 = gdn::OutLds<E, DK, DV>::bytes;
     std::call_once(attr_once, [&] {
         const struct {
             const void *fn;
             size_t bytes;
         } dyn[] = {
             {(const void *)gdn::gdn_wy_kernel<E, DK, DV>, lds1},
-            {output_fn<E, DK, DV>(), lds3},
             {scan1, L1::bytes},
             {scan2, L2::bytes},
             {scant, LT::bytes},
         };
         for (const auto &d : dyn) {
-            if (!d.fn) continue;
             const hipError_t e =
                 hipFuncSetAttribute(d.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)d.bytes);
             if (e != hipSuccess && attr_err == hipSuccess) attr_err = e;
@@ -282,17 +259,15 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
         case 2:
             return launch((const void *)gdn::gdn_groupscan_kernel<E, DK, DV>, dim3(groups(DV / 16, BH)),
                           dim3(64 * gdn::kScanSplit), 0, s, p);
-        case 3:
+        default:
             if (wide)
                 return launch(scan2, dim3(groups(DV / (16 * CTW), BH * p.NG)), dim3(gdn::scan_threads<NOW>()), L2::bytes, s, p);
             return launch(scan1, dim3(groups(DV / 16, BH * p.NG)), dim3(gdn::scan_threads<NOW>()), L1::bytes, s, p);
-        default:
-            return launch(output_fn<E, DK, DV>(), dim3(p.NC, BH), dim3(256), lds3, s, p);
         }
     };
     hipError_t er = hipSuccess;
     for (int i = 0; i < kStages && er == hipSuccess; ++i) {
-        const bool runs = (i == 1 || i == 2) ? p.NG > 1 : (i == 4 ? sizeof(E) == 4 : true);
+        const bool runs = (i == 1 || i == 2) ? p.NG > 1 : i != 4;
         if (tm) tm->ran[i] = runs;
         if (!runs) continue;
         if (!tm) {

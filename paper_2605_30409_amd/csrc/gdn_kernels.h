@@ -18,16 +18,13 @@
 // s > r masked before the exp.
 //
 // Workspace per (b*H + h, chunk) -- see gdn_api.hip for the byte layout:
-//   g  [64]       fp64   cumulative log decay (fp64 so that g_r - g_s keeps
-//                        its precision when the decay over a chunk is huge;
-//                        written on the fp32 path only)
 //   gf [68]       fp32   e^{g_C - g_r} (the update's per-token key scale),
 //                        then g_C, the log decay over the chunk, as one fp64,
 //                        and gamma = e^{g_C}
 //   W  64*Dk      E      -W (the WY factor, negated), fragment-major for the scan
 //   Ut Dv*64      E      Ut, fragment-major
-//   Hs [Dv][Dk]   E      H_{c-1}^T, the state entering the chunk
-//   Us [Dv][64]   E      U^T
+//   Qf 64*Dk      E      diag(e^g) Q, row fragments for the output
+//   Pf 64*64      E      (Q K^T o M), row fragments for the output
 // "Fragment-major" means the exact per-lane order in which the scan's MFMAs
 // consume the operand, so every scan load is one contiguous wave access:
 //   W  [Dk/64 wave][4 token tile][2 k block][64 lane][8]
@@ -55,13 +52,8 @@ template <class E> struct Params {
     int B, H, T, NC;
     int c0;           // first chunk of this launch; chunk indices below count from it, up to NC
     int G, NG;        // chunks per scan group, number of groups
-    double *g;
     float *gf;        // per (b*H + h, chunk): e^{g_C - g_r} [64], g_C (fp64), e^{g_C}, 1 unused
-    E *W, *Ut, *Hs, *Us;
-    // bf16: the scan computes the output, from Qf = diag(e^g) Q and
-    // Pf = (Q K^T o M) row fragments written by the WY kernel (in the Hs / Us
-    // workspace regions, which only the fp32 path uses as such; nor is g needed).
-    E *Qf, *Pf;
+    E *W, *Ut, *Qf, *Pf;
     E *Nf;            // per (b*H + h, group): N_g = Phi_g - Gamma_g I, fragment-major
     float *PsiT;      // per (b*H + h, group): Psi_g^T [Dv][Dk]
     double *lgam;     // per (b*H + h, group): log Gamma_g
@@ -93,7 +85,9 @@ template <class E, int DK, int DV> struct WyLds {
     // waves per SIMD when as many eight-wave workgroups as fit in 160 KB share
     // a CU (the register budget the kernel is compiled for)
     static constexpr int fit = (int)((160 * 1024) / bytes);
-    static constexpr int waves_per_simd = fit >= 4 ? 8 : (fit < 1 ? 2 : 2 * fit);
+    // (fp32: at most two, its fragments spill in the registers of a third)
+    static constexpr int cap = sizeof(E) == 4 && fit > 2 ? 2 : fit;
+    static constexpr int waves_per_simd = cap >= 4 ? 8 : (cap < 1 ? 2 : 2 * cap);
 };
 
 // Decay ratio e^{g_r - g_s} (s <= r) inside the WY kernel.  The fp32 path
@@ -191,7 +185,6 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
         sgl[l] = (float)(g * kLog2e);
         sb[l] = be;
         sw[l] = -be * eg;
-        if (sizeof(E) == 4) p.g[cidx * kChunk + l] = g;  // the fp32 output kernel reads it
         p.gf[cidx * kGateRec + l] = __builtin_amdgcn_exp2f((float)((gC - g) * kLog2e));
         if (l == 0) {
             *(double *)(p.gf + cidx * kGateRec + kChunk) = gC;
@@ -204,13 +197,11 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
         *(uint4 *)(sK + r * L::LDK + cv * VE) = kreg[n];
     }
     lds_barrier();
-    if constexpr (sizeof(E) == 2) {
-        if (qjob) {
+    if (qjob) {
 #pragma unroll
-            for (int kb = 0; kb < DK / 32; ++kb)
-                qf[kb] = rq < nvalid ? load_frag<E>(p.q + (row0 + rq * rstride) * DK + 32 * kb, lg)
-                                     : TR::cat(TR::zero(), TR::zero());
-        }
+        for (int kb = 0; kb < DK / 32; ++kb)
+            qf[kb] = rq < nvalid ? load_frag<E>(p.q + (row0 + rq * rstride) * DK + 32 * kb, lg)
+                                 : TR::cat(TR::zero(), TR::zero());
     }
 #pragma unroll
     for (int n = 0; n < NVV; ++n) {
@@ -268,36 +259,34 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
         // the row fragments (B operands over d, resp. s) of the fused output.
         // P^T tiles take their s rows in P32 order, so a tile pair is one
         // fragment; block m = 1 only matters for r >= 32.
-        if constexpr (sizeof(E) == 2) {
-            if (qjob) {
-                if (qjob_m == 0) {
-                    const float er = expf((float)sg[rq]);
-                    E *Qf = p.Qf + cidx * (size_t)kChunk * DK + l * 8;
+        if (qjob) {
+            if (qjob_m == 0) {
+                const float er = expf((float)sg[rq]);
+                E *Qf = p.Qf + cidx * (size_t)kChunk * DK + l * 8;
 #pragma unroll
-                    for (int kb = 0; kb < DK / 32; ++kb) {
-                        const f32x4 lo = TR::to_f32(TR::lo(qf[kb])) * er, hi = TR::to_f32(TR::hi(qf[kb])) * er;
-                        TR::store8(Qf + (size_t)(qjob_rt * (DK / 32) + kb) * 512,
-                                   TR::cat(TR::from_f32(lo), TR::from_f32(hi)));
-                    }
+                for (int kb = 0; kb < DK / 32; ++kb) {
+                    const f32x4 lo = TR::to_f32(TR::lo(qf[kb])) * er, hi = TR::to_f32(TR::hi(qf[kb])) * er;
+                    TR::store8(Qf + (size_t)(qjob_rt * (DK / 32) + kb) * 512,
+                               TR::cat(TR::from_f32(lo), TR::from_f32(hi)));
                 }
-                E *Pf = p.Pf + cidx * (size_t)kChunk * kChunk + l * 8;
-                const int m = qjob_m;
-                typename TR::quad pq[2];
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int kb = 0; kb < DK / 32; ++kb)
-                        acc = TR::mma(load_frag<E>(sK + (32 * m + p32_row(a, li)) * L::LDK + 32 * kb, lg), qf[kb], acc);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int s2 = 32 * m + 8 * lg + 4 * a + q;
-                        acc[q] = (s2 <= rq) ? wy_decay<E>(sg, sgl, rq, s2) * acc[q] : 0.f;
-                    }
-                    pq[a] = TR::from_f32(acc);
-                }
-                TR::store8(Pf + (size_t)(qjob_rt * 2 + m) * 512, TR::cat(pq[0], pq[1]));
             }
+            E *Pf = p.Pf + cidx * (size_t)kChunk * kChunk + l * 8;
+            const int m = qjob_m;
+            typename TR::quad pq[2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kb = 0; kb < DK / 32; ++kb)
+                    acc = TR::mma(load_frag<E>(sK + (32 * m + p32_row(a, li)) * L::LDK + 32 * kb, lg), qf[kb], acc);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int s2 = 32 * m + 8 * lg + 4 * a + q;
+                    acc[q] = (s2 <= rq) ? wy_decay<E>(sg, sgl, rq, s2) * acc[q] : 0.f;
+                }
+                pq[a] = TR::from_f32(acc);
+            }
+            TR::store8(Pf + (size_t)(qjob_rt * 2 + m) * 512, TR::cat(pq[0], pq[1]));
         }
     }
     lds_barrier();
@@ -409,8 +398,7 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
 //   (S) gdn_groupscan_kernel: H <- Phi_g H + Psi_g over the groups, recording
 //       every group's entry state (and the final state);
 //   (O) gdn_chunkscan_kernel<.., SCAN_STATES>: for every group in parallel, run
-//       the recurrence from the group's true entry state and write the
-//       per-chunk state H_{c-1} and pseudo-values U_c the output stage needs.
+//       the recurrence from the group's true entry state and form the output.
 // With a single group only (O) runs, from state_in, and writes state_out.
 //
 // gdn_chunkscan_kernel: a workgroup owns 16 * CT state columns of one
@@ -426,7 +414,7 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
 // A phase is one LDS round trip, one short chain of MFMAs and a few
 // conversions; with the rows on one wave the step was 36 MFMAs and 80 VALU
 // instructions in a row on one SIMD while three others had nothing to do.
-// NOW output waves (bf16) read the same H and U operands and form the output of
+// NOW output waves read the same H and U operands and form the output of
 // 4 / NOW token tiles each: Q~ H in phase 1, + P U and the store in phase 2.
 //
 // -W and U~t go straight from the workspace to the registers of the wave that
@@ -446,7 +434,8 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
 // tile: 0.56 us of dependent MFMAs and VALU a step, 0.72 with the loads.  So where
 // that one CU's intake is the limit the kernel is as fast as before (40 us), and
 // where the chain was, faster: fp32 (256 MFMAs of 32 cycles a step and tile, now
-// over four SIMDs) T = 3557, H = 16 250 -> 87 us; the grouped passes of two
+// over four SIMDs) T = 3557, H = 16 250 -> 104 us, and 143 with the output in it
+// where a kernel of its own took 83 more; the grouped passes of two
 // heads at T = 10560 18.4 -> 12 us (transfers) and 22.9 + 9.6 -> 13 us (states,
 // which then formed the output in a kernel of its own); D = 64 x 80 heads, with
 // two column tiles per workgroup, 307 -> 174 us.
@@ -564,10 +553,10 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
     using quad = typename TR::quad;
     using L = ScanLds<E, DK, CT, NOW>;
     using X = Xch<E>;
-    static_assert(!NOW || PHASE == SCAN_STATES, "the output is fused into the state pass only");
+    static_assert((NOW > 0) == (PHASE == SCAN_STATES), "the state pass forms the output");
     constexpr int D = L::DEPTH, NCW = kScanSplit;
     constexpr int KB = L::KB, NT = L::NT, RT = NT / NCW; // row tiles per compute wave
-    constexpr int NWS = sizeof(E) == 4 && CT > 1 ? 2 : 4; // register sets of W and U~t (fp32 pairs: no room for four)
+    constexpr int NWS = sizeof(E) == 4 ? 2 : 4;          // register sets of W and U~t (fp32: no room for four)
     constexpr int WGC = 16 * CT;                         // columns per workgroup
     constexpr int WCOLS = PHASE == SCAN_TRANS ? DK + DV : DV;
     constexpr int NJB = WCOLS / WGC;                     // column blocks per (b, h, group)
@@ -685,7 +674,8 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
                 frag q[RO][KB], p[RO][2];
             };
             // Operands are requested two chunks ahead, in three register sets
-            // used in turn (past the end: the last chunk's, not used), a part of
+            // used in turn (fp32, with longer steps and larger operands: one
+            // ahead, in two sets; past the end: the last chunk's, not used), a part of
             // them at the start of either phase so that neither waits for the
             // issue.  Addresses are a uniform base and a 32-bit lane offset.
             const unsigned lo16 = 16u * l * (sizeof(frag) / 16);
@@ -767,25 +757,35 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
                 }
                 obase += kChunk * ostride;
             };
-            Set s0, s1, s2;
-            load_q(s0, 0, KB);
-            load_p(s0);
-            load_q(s1, 0, KB);
-            load_p(s1);
-            // Whole chunks three at a time, without a branch (a branch around the
+            // Whole chunks a few at a time, without a branch (a branch around the
             // stores or out of the loop makes the compiler wait for operands that
             // are not needed yet); the rest, the sequence's last chunk among it,
             // one by one.
             const int c_whole = min(c_end, p.T / kChunk - p.c0);
             int c = c_begin;
-            for (; c + 3 <= c_whole; c += 3) {
-                chunk(c, s0, s2, std::true_type{});
-                chunk(c + 1, s1, s0, std::true_type{});
-                chunk(c + 2, s2, s1, std::true_type{});
+            Set s0, s1;
+            load_q(s0, 0, KB);
+            load_p(s0);
+            if constexpr (sizeof(E) == 4) {
+                for (; c + 2 <= c_whole; c += 2) {
+                    chunk(c, s0, s1, std::true_type{});
+                    chunk(c + 1, s1, s0, std::true_type{});
+                }
+                if (c < c_end) chunk(c, s0, s1, std::false_type{});
+                if (c + 1 < c_end) chunk(c + 1, s1, s0, std::false_type{});
+            } else {
+                Set s2;
+                load_q(s1, 0, KB);
+                load_p(s1);
+                for (; c + 3 <= c_whole; c += 3) {
+                    chunk(c, s0, s2, std::true_type{});
+                    chunk(c + 1, s1, s0, std::true_type{});
+                    chunk(c + 2, s2, s1, std::true_type{});
+                }
+                if (c < c_end) chunk(c, s0, s2, std::false_type{});
+                if (c + 1 < c_end) chunk(c + 1, s1, s0, std::false_type{});
+                if (c + 2 < c_end) chunk(c + 2, s2, s1, std::false_type{});
             }
-            if (c < c_end) chunk(c, s0, s2, std::false_type{});
-            if (c + 1 < c_end) chunk(c + 1, s1, s0, std::false_type{});
-            if (c + 2 < c_end) chunk(c + 2, s2, s1, std::false_type{});
             lds_only_barrier();                          // matches the loaders' last barrier
             return;
         }
@@ -830,9 +830,8 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
     }
     double lgam = 0.0;  // sum of gC over the group (SCAN_TRANS)
 
-    // H rounded to E into LDS, as the B operands over its 32-row blocks; with
-    // the output in its own kernel also the state entering chunk c, to Hs
-    auto put_h = [&](int c) {
+    // H rounded to E into LDS, as the B operands over its 32-row blocks
+    auto put_h = [&]() {
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
             quad hq[RT];
@@ -842,13 +841,6 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
                 X::put2(hx, ct * KB + s, l, hq[0], hq[1]);
             else
                 X::put(hx, ct * KB + (s >> 1), s & 1, l, hq[0]);
-            if constexpr (PHASE == SCAN_STATES && !NOW) {
-                if (c < c_end) {
-                    E *Hs = p.Hs + (((size_t)bh * p.NC + c) * DV + col(ct)) * DK;
-#pragma unroll
-                    for (int i = 0; i < RT; ++i) TR::store(Hs + row0(i), hq[i]);
-                }
-            }
         }
     };
     // this wave's U~t quads: tokens 32 m + 8 lg + 4 a + q (s = 2 m + a); requested
@@ -884,7 +876,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
     // H_c = gamma H_{c-1} + K^T (diag(e^{g_C - g}) U).
     // Chunk c_begin + j sits in slot j % D and its W and U~t in set j % NWS, so with
     // four steps in a row every LDS address is a constant.
-    auto step = [&](int c, auto j_, quad (&us)[CT], frag (&wf)[KB]) {
+    auto step = [&](auto j_, quad (&us)[CT], frag (&wf)[KB]) {
         constexpr int J = decltype(j_)::value;
         lds_only_barrier();                              // B1(c)
         const unsigned char *sl = scan_lds + (J % D) * L::SLOT;
@@ -916,12 +908,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
             X::put(ux, ct * 2 + (s >> 1), s & 1, l, TR::from_f32(u[ct] * dsc));
-            const quad uq = TR::from_f32(u[ct]);
-            if constexpr (NOW > 0) X::put(uo, ct * 2 + (s >> 1), s & 1, l, uq);
-            if constexpr (PHASE == SCAN_STATES && !NOW)
-                TR::store(p.Us + (((size_t)bh * p.NC + c) * DV + col(ct)) * kChunk + 32 * (s >> 1) + 8 * lg +
-                              4 * (s & 1),
-                          uq);
+            if constexpr (NOW > 0) X::put(uo, ct * 2 + (s >> 1), s & 1, l, TR::from_f32(u[ct]));
         }
 #pragma unroll
         for (int i = 0; i < RT; ++i)
@@ -941,7 +928,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
             for (int i = 0; i < RT; ++i)
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) Hacc[i][ct] = TR::mma(kf[i][m], uk[m][ct], Hacc[i][ct]);
-        put_h(c + 1);
+        put_h();
     };
     quad us[NWS][CT];
     frag wf[NWS][KB];
@@ -950,21 +937,21 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
         load_w(wf[i]);
         load_us(us[i]);
     }
-    put_h(c_begin);
+    put_h();
     int c = c_begin;
     const std::integral_constant<int, 0> j0{};
     const std::integral_constant<int, 1> j1{};
     const std::integral_constant<int, 2> j2{};
     const std::integral_constant<int, 3> j3{};
     for (; c + 4 <= c_end; c += 4) {
-        step(c, j0, us[0 % NWS], wf[0 % NWS]);
-        step(c + 1, j1, us[1 % NWS], wf[1 % NWS]);
-        step(c + 2, j2, us[2 % NWS], wf[2 % NWS]);
-        step(c + 3, j3, us[3 % NWS], wf[3 % NWS]);
+        step(j0, us[0 % NWS], wf[0 % NWS]);
+        step(j1, us[1 % NWS], wf[1 % NWS]);
+        step(j2, us[2 % NWS], wf[2 % NWS]);
+        step(j3, us[3 % NWS], wf[3 % NWS]);
     }
-    if (c < c_end) step(c, j0, us[0 % NWS], wf[0 % NWS]);
-    if (c + 1 < c_end) step(c + 1, j1, us[1 % NWS], wf[1 % NWS]);
-    if (c + 2 < c_end) step(c + 2, j2, us[2 % NWS], wf[2 % NWS]);
+    if (c < c_end) step(j0, us[0 % NWS], wf[0 % NWS]);
+    if (c + 1 < c_end) step(j1, us[1 % NWS], wf[1 % NWS]);
+    if (c + 2 < c_end) step(j2, us[2 % NWS], wf[2 % NWS]);
     lds_only_barrier();  // the loaders have drained: the ring is free
 
     const size_t gidx = (size_t)bh * p.NG + grp;
@@ -1119,138 +1106,6 @@ void gdn_groupscan_kernel(Params<E> p) {
         for (int i = 0; i < RT; ++i)
 #pragma unroll
             for (int q = 0; q < 4; ++q) p.state_out[((size_t)bh * DK + row0(i) + q) * DV + j] = Hacc[i][q];
-    }
-}
-
-// --------------------------------------------------------------------------
-// Stage 3: per-chunk output.  Grid (NC, B*H), 256 threads; wave w produces
-// tokens 16w..16w+15 of the chunk for all Dv columns, as O^T tiles:
-//   O^T = H_{c-1}^T Q^T diag(e^g) + U^T P^T,   P^T[s][r] = e^{g_r-g_s} k_s.q_r (s <= r)
-// --------------------------------------------------------------------------
-template <class E, int DK, int DV> struct OutLds {
-    static constexpr int PAD = 16 / (int)sizeof(E);
-    static constexpr int LDH = DK + PAD;
-    static constexpr int LDU = kChunk + PAD;
-    static constexpr int LDK = DK + PAD;
-    static constexpr size_t oH = 0;
-    static constexpr size_t oU = oH + sizeof(E) * DV * LDH;
-    static constexpr size_t oK = oU + sizeof(E) * DV * LDU;
-    static constexpr size_t oG = oK + sizeof(E) * kChunk * LDK;
-    static constexpr size_t bytes = oG + 8 * kChunk;
-};
-
-template <class E, int DK, int DV>
-__global__ __launch_bounds__(256) void gdn_output_kernel(Params<E> p) {
-    using L = OutLds<E, DK, DV>;
-    using TR = Tr<E>;
-    using frag = typename TR::frag;
-    using quad = typename TR::quad;
-    constexpr int VE = 16 / (int)sizeof(E);            // elements per 16-byte vector
-    constexpr int NH = DV * DK / VE / 256;             // H^T vectors per thread
-    constexpr int NU = DV * kChunk / VE / 256;         // U^T vectors per thread
-    constexpr int NK = kChunk * DK / VE / 256;         // K vectors per thread
-    extern __shared__ __align__(16) unsigned char smem[];
-    E *sH = (E *)(smem + L::oH);
-    E *sU = (E *)(smem + L::oU);
-    E *sK = (E *)(smem + L::oK);
-    double *sg = (double *)(smem + L::oG);
-
-    const int c = blockIdx.x, bh = blockIdx.y;
-    const int b = bh / p.H, h = bh - b * p.H;
-    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, li = l & 15, lg = l >> 4;
-    const int t0 = (p.c0 + c) * kChunk;
-    const int nvalid = min(kChunk, p.T - t0);
-    const size_t cidx = (size_t)bh * p.NC + c;
-    const size_t row0 = ((size_t)b * p.T + t0) * p.H + h;
-    const size_t rstride = (size_t)p.H;
-
-    // Every global load is issued before the first LDS store, so their
-    // latencies overlap: Q rows of this wave's tokens as B operands
-    // (B[k=d][n=r] = Q[r][d]; padded tokens are 0), then H^T, U^T and K
-    // rows with 16-byte coalesced loads.
-    const int r = 16 * w + li;  // token within the chunk
-    const bool rvalid = r < nvalid;
-    frag qf[DK / 32];
-#pragma unroll
-    for (int kb = 0; kb < DK / 32; ++kb)
-        qf[kb] = rvalid ? load_frag<E>(p.q + (row0 + r * rstride) * DK + 32 * kb, lg) : TR::cat(TR::zero(), TR::zero());
-    uint4 hreg[NH], ureg[NU], kreg[NK];
-    const E *Hs = p.Hs + cidx * (size_t)DV * DK;
-    const E *Us = p.Us + cidx * (size_t)DV * kChunk;
-#pragma unroll
-    for (int n = 0; n < NH; ++n) hreg[n] = *(const uint4 *)(Hs + (size_t)(tid + 256 * n) * VE);
-#pragma unroll
-    for (int n = 0; n < NU; ++n) ureg[n] = *(const uint4 *)(Us + (size_t)(tid + 256 * n) * VE);
-#pragma unroll
-    for (int n = 0; n < NK; ++n) {
-        const int idx = tid + 256 * n, kr = idx / (DK / VE), kc = idx % (DK / VE);
-        kreg[n] = kr < nvalid ? *(const uint4 *)(p.k + (row0 + kr * rstride) * DK + kc * VE) : make_uint4(0u, 0u, 0u, 0u);
-    }
-    if (tid < kChunk) sg[tid] = p.g[cidx * kChunk + tid];
-#pragma unroll
-    for (int n = 0; n < NH; ++n) {
-        const int idx = tid + 256 * n;
-        *(uint4 *)(sH + (idx / (DK / VE)) * L::LDH + (idx % (DK / VE)) * VE) = hreg[n];
-    }
-#pragma unroll
-    for (int n = 0; n < NU; ++n) {
-        const int idx = tid + 256 * n;
-        *(uint4 *)(sU + (idx / (kChunk / VE)) * L::LDU + (idx % (kChunk / VE)) * VE) = ureg[n];
-    }
-#pragma unroll
-    for (int n = 0; n < NK; ++n) {
-        const int idx = tid + 256 * n;
-        *(uint4 *)(sK + (idx / (DK / VE)) * L::LDK + (idx % (DK / VE)) * VE) = kreg[n];
-    }
-    lds_barrier();
-
-    // P^T tiles in P32 order (tile st = 2 m + a holds tokens 32 m + p32_row(a, i)),
-    // masked (s <= r) and decayed, rounded to E.  Block m = 1 only matters for r >= 32.
-    const double gr = sg[r];
-    quad pq[4];
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-        const int m = st >> 1, a = st & 1;
-        pq[st] = TR::zero();
-        if (m == 0 || w >= 2) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kb = 0; kb < DK / 32; ++kb)
-                acc = TR::mma(load_frag<E>(sK + (32 * m + p32_row(a, li)) * L::LDK + 32 * kb, lg),
-                              qf[kb], acc);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int s2 = 32 * m + 8 * lg + 4 * a + q;
-                acc[q] = (s2 <= r) ? expf((float)(gr - sg[s2])) * acc[q] : 0.f;
-            }
-            pq[st] = TR::from_f32(acc);
-        }
-    }
-    const frag pf0 = TR::cat(pq[0], pq[1]);
-    const frag pf1 = TR::cat(pq[2], pq[3]);
-    const float er = expf((float)gr);
-
-    // O^T = H^T Q^T e^{g_r} + U^T P^T in 32-column blocks J; the two tiles a of
-    // a block take A rows (output columns) 32 J + p32_row(a, i), so lane
-    // (li, lg) ends up with the 8 consecutive columns 32 J + 8 lg + [0, 8) of
-    // token r and writes them with one 16-byte store.
-    E *orow = p.out + (row0 + r * rstride) * DV;
-#pragma unroll 2
-    for (int J = 0; J < DV / 32; ++J) {
-        f32x4 acc[2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            const int col = 32 * J + p32_row(a, li);
-            f32x4 x = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kb = 0; kb < DK / 32; ++kb)
-                x = TR::mma(load_frag<E>(sH + col * L::LDH + 32 * kb, lg), qf[kb], x);
-            x *= er;
-            x = TR::mma(load_frag<E>(sU + col * L::LDU, lg), pf0, x);
-            if (w >= 2) x = TR::mma(load_frag<E>(sU + col * L::LDU + 32, lg), pf1, x);
-            acc[a] = x;
-        }
-        if (rvalid) TR::store8(orow + 32 * J + 8 * lg, TR::cat(TR::from_f32(acc[0]), TR::from_f32(acc[1])));
     }
 }
 
