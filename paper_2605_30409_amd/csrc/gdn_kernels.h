@@ -591,12 +591,11 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
 
     if (w >= NCW + NOW) {
         // ---------------- loader waves ----------------
-        // A wave needs some 50 cycles to issue a 1 KB copy, so a chunk's copies
-        // are dealt to four waves (two for W, two for K) and each issues half of
-        // its share in either phase: no phase waits for the issue.  Past the end
-        // the loaders still issue the same number of copies (so that the counts
-        // the waits rely on are constant), reading the last chunk, into the slot
-        // of the missing chunk.
+        // A wave needs some 50 cycles to issue a 1 KB copy, so a chunk's copies are
+        // dealt to two waves and each issues half of its share in either phase: no
+        // phase waits for the issue.  Past the end the loaders still issue the same
+        // number of copies (so that the counts the waits rely on are constant),
+        // reading the last chunk, into the slot of the missing chunk.
         const int part = w - NCW - NOW;
         constexpr int NS = L::NC_W / 2, NH = NS / 2;     // copies per wave and chunk, and per phase
         {

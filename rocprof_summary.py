@@ -32,23 +32,21 @@ def short(name):
 
 def stage_of(kernel):
     """The library's stage name for a kernel (token path: wy, group_transfer,
-    group_scan, chunk_states, output; frame-wise path: summaries, reduce, scan,
+    group_scan, chunk_states; frame-wise path: summaries, reduce, scan,
     output)."""
     k = short(kernel)
-    if k.startswith("gdn_frame_summary"):          # gdn_frame_summary_kernel, fused variant too
+    if k.startswith(("gdn_frame_summary", "gdn_frame_rope", "gdn_frame_kfeatures")):
         return "summaries"
     if k.startswith("gdn_frame_reduce"):
         return "reduce"
     if k.startswith("gdn_frame_scan"):
         return "scan"
-    if k.startswith("gdn_frame_output"):           # gdn_frame_output_kernel, gdn_frame_output_fused_kernel
+    if k.startswith("gdn_frame_output"):           # the plain kernel and both fused ones
         return "output"
     if k.startswith("gdn_wy_kernel"):
         return "wy"
     if k.startswith("gdn_groupscan_kernel"):
         return "group_scan"
-    if k.startswith("gdn_output_kernel"):
-        return "output"
     if k.startswith("gdn_chunkscan_kernel"):
         args = [a.strip() for a in k.split("<", 1)[1].rstrip(">").split(",")]
         return "group_transfer" if args[3] == "0" else "chunk_states"
