@@ -17,7 +17,7 @@ using gdn::kChunk;
 using gdn::kGateRec;
 
 struct WsLayout {
-    size_t g, gf, W, Ut, Hs, Us, Nf, PsiT, lgam, HgT, total;
+    size_t er, gf, W, Ut, Hs, Us, Nf, PsiT, lgam, HgT, total;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -43,6 +43,10 @@ int resolve_group(int NC, long long BH, int Dv, int group, bool bf16) {
     return group > NC ? NC : group;
 }
 
+// fp32, and bf16 with several scan groups: the output takes the queries unscaled
+// (the kernels' RAW variant).
+bool raw_queries(size_t esz, int NG) { return esz == 4 || NG > 1; }
+
 WsLayout ws_layout(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
     const int NC = num_chunks(T);
     const int NG = (NC + G - 1) / G;
@@ -51,15 +55,15 @@ WsLayout ws_layout(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
     const size_t ngr = NG > 1 ? bh * NG : 0;
     WsLayout L;
     size_t off = 0;
-    L.g = off;    off = align256(off + nch * kChunk * 8);
+    L.er = off;   off = align256(off + nch * kChunk * 8);
     L.gf = off;   off = align256(off + nch * kGateRec * 4);
     L.W = off;    off = align256(off + nch * kChunk * Dk * esz);
     L.Ut = off;   off = align256(off + nch * Dv * kChunk * esz);
-    // These regions hold the chunk's decay-scaled queries (C x Dk) and masked
-    // scores (C x C).  In fp32 and with several groups they keep the sizes of the
-    // per-chunk state (Dv x Dk) and pseudo-values (Dv x C) that an output kernel
-    // of its own once read there, and g its place: a caller's workspace is sized
-    // the same as ever.
+    // These regions hold the chunk's queries (C x Dk) and masked scores (C x C).
+    // In fp32 and with several groups they keep the sizes of the per-chunk state
+    // (Dv x Dk) and pseudo-values (Dv x C) that an output kernel of its own once
+    // read there, and er those of its fp64 log decays (a single bf16 scan has no
+    // use for er): a caller's workspace is sized the same as ever.
     const bool fused = esz == 2 && NG == 1;
     L.Hs = off;   off = align256(off + nch * (fused ? kChunk : Dv) * Dk * esz);
     L.Us = off;   off = align256(off + nch * (fused ? kChunk : Dv) * kChunk * esz);
@@ -77,7 +81,7 @@ WsLayout ws_layout(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
 // the highest element offset touched, plus the element's width.  0 if no
 // kernel of the path uses the region.
 struct WsNeeds {
-    size_t g, gf, W, Ut, Hs, Us, Nf, PsiT, lgam, HgT;
+    size_t er, gf, W, Ut, Hs, Us, Nf, PsiT, lgam, HgT;
 };
 
 WsNeeds ws_needs(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
@@ -86,6 +90,8 @@ WsNeeds ws_needs(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
     const size_t gmax = (size_t)B * H * NG - 1;             // last group record
     const size_t KB = (size_t)Dk / 32, NJ = (size_t)Dv / 16;
     WsNeeds n{};
+    // WY kernel (fp32, and bf16 with several groups): er[cidx * 64 + r]
+    if (raw_queries(esz, (int)NG)) n.er = (cmax * kChunk + kChunk) * 4;
     // WY kernel: gf[cidx * 68 + l] and the fp64 g_C at gf + cidx * 68 + 64 (the
     // scan copies gf[cidx * 68 + 4 l .. + 3], l < 17)
     n.gf = (cmax * kGateRec + kGateRec) * 4;
@@ -176,6 +182,7 @@ gdn::Params<E> make_params(const void *q, const void *k, const void *v, const fl
     p.NG = (p.NC + G - 1) / G;
     const WsLayout L = ws_layout(B, H, T, Dk, Dv, sizeof(E), G);
     unsigned char *base = (unsigned char *)ws;
+    p.er = (float *)(base + L.er);
     p.gf = (float *)(base + L.gf);
     p.W = (E *)(base + L.W);
     p.Ut = (E *)(base + L.Ut);
@@ -208,7 +215,7 @@ struct StageTiming {
     bool ran[kStages];
 };
 
-template <class E, int DK, int DV>
+template <class E, int DK, int DV, bool RAW>
 hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) {
     constexpr int NOW = 4;                       // output waves
     // Two column tiles per workgroup once one each would be more workgroups than
@@ -223,9 +230,9 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
     using L1 = gdn::ScanLds<E, DK, 1, NOW>;
     using L2 = gdn::ScanLds<E, DK, CTW, NOW>;
     using LT = gdn::ScanLds<E, DK, 2, 0>;        // group transfers
-    const void *scan1 = (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, 1, NOW>;
-    const void *scan2 = (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, CTW, NOW>;
-    const void *scant = (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_TRANS, 2, 0>;
+    const void *scan1 = (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, 1, NOW, RAW>;
+    const void *scan2 = (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_STATES, CTW, NOW, RAW>;
+    const void *scant = (const void *)gdn::gdn_chunkscan_kernel<E, DK, DV, gdn::SCAN_TRANS, 2, 0, true>;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     const size_t lds1 = gdn::WyLds<E, DK, DV>::bytes;
@@ -234,7 +241,7 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
             const void *fn;
             size_t bytes;
         } dyn[] = {
-            {(const void *)gdn::gdn_wy_kernel<E, DK, DV>, lds1},
+            {(const void *)gdn::gdn_wy_kernel<E, DK, DV, RAW>, lds1},
             {scan1, L1::bytes},
             {scan2, L2::bytes},
             {scant, LT::bytes},
@@ -252,7 +259,7 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
     auto stage = [&](int i) -> hipError_t {
         switch (i) {
         case 0:
-            return launch((const void *)gdn::gdn_wy_kernel<E, DK, DV>, dim3(p.NC * BH), dim3(64 * gdn::kWyWaves),
+            return launch((const void *)gdn::gdn_wy_kernel<E, DK, DV, RAW>, dim3(p.NC * BH), dim3(64 * gdn::kWyWaves),
                           lds1, s, p);
         case 1:
             return launch(scant, dim3(groups((DK + DV) / 32, BH * p.NG)), dim3(gdn::scan_threads<0>()), LT::bytes, s, p);
@@ -281,12 +288,19 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
     return er;
 }
 
+template <class E, bool RAW>
+hipError_t dispatch_raw(const gdn::Params<E> &p, int Dk, int Dv, hipStream_t s, StageTiming *tm) {
+    if (Dk == 128 && Dv == 128) return launch_path<E, 128, 128, RAW>(p, s, tm);
+    if (Dk == 64 && Dv == 64) return launch_path<E, 64, 64, RAW>(p, s, tm);
+    if (Dk == 128 && Dv == 64) return launch_path<E, 128, 64, RAW>(p, s, tm);
+    return launch_path<E, 64, 128, RAW>(p, s, tm);
+}
+
 template <class E>
 hipError_t dispatch(const gdn::Params<E> &p, int Dk, int Dv, hipStream_t s, StageTiming *tm) {
-    if (Dk == 128 && Dv == 128) return launch_path<E, 128, 128>(p, s, tm);
-    if (Dk == 64 && Dv == 64) return launch_path<E, 64, 64>(p, s, tm);
-    if (Dk == 128 && Dv == 64) return launch_path<E, 128, 64>(p, s, tm);
-    return launch_path<E, 64, 128>(p, s, tm);
+    if constexpr (sizeof(E) == 2)
+        if (!raw_queries(sizeof(E), p.NG)) return dispatch_raw<E, false>(p, Dk, Dv, s, tm);
+    return dispatch_raw<E, true>(p, Dk, Dv, s, tm);
 }
 
 // A single-group call whose chunk records (W, U~, Q~, P: 56 KB a chunk and head at
@@ -944,8 +958,8 @@ int gdn_workspace_check(int B, int H, int T, int Dk, int Dv, int chunk, int is_b
     const int G = resolve_group(num_chunks(T), (long long)B * H, Dv, scan_group, is_bf16 != 0);
     const WsLayout L = ws_layout(B, H, T, Dk, Dv, esz, G);
     const WsNeeds n = ws_needs(B, H, T, Dk, Dv, esz, G);
-    const size_t start[] = {L.g, L.gf, L.W, L.Ut, L.Hs, L.Us, L.Nf, L.PsiT, L.lgam, L.HgT, L.total};
-    const size_t need[] = {n.g, n.gf, n.W, n.Ut, n.Hs, n.Us, n.Nf, n.PsiT, n.lgam, n.HgT};
+    const size_t start[] = {L.er, L.gf, L.W, L.Ut, L.Hs, L.Us, L.Nf, L.PsiT, L.lgam, L.HgT, L.total};
+    const size_t need[] = {n.er, n.gf, n.W, n.Ut, n.Hs, n.Us, n.Nf, n.PsiT, n.lgam, n.HgT};
     for (int r = 0; r < 10; ++r) {
         if (start[r] % 256) return r + 1;                    // regions start 256-byte aligned
         if (need[r] > start[r + 1] - start[r]) return r + 1;  // region too small

@@ -23,14 +23,21 @@
 //                        and gamma = e^{g_C}
 //   W  64*Dk      E      -W (the WY factor, negated), fragment-major for the scan
 //   Ut Dv*64      E      Ut, fragment-major
-//   Qf 64*Dk      E      diag(e^g) Q, row fragments for the output
+//   Qf 64*Dk      E      diag(e^g) Q, row fragments for the output (RAW: Q itself)
 //   Pf 64*64      E      (Q K^T o M), row fragments for the output
+//   er 64         fp32   RAW only: e^{g_r}
 // "Fragment-major" means the exact per-lane order in which the scan's MFMAs
 // consume the operand, so every scan load is one contiguous wave access:
 //   W  [Dk/64 wave][4 token tile][2 k block][64 lane][8]
 //        = -W[32 m + p32_row(a, li)][64 wave + 32 kb + 8 lg + e]    (tile 2 m + a)
 //   Ut [Dv/16 column tile][4 token tile][64 lane][4]
 //        = Ut[32 m + 8 lg + 4 a + e][16 jt + li]                      (tile 2 m + a)
+// RAW (fp32, and bf16 with several scan groups): the output's products take the
+// queries as they are given and e^{g_r} multiplies their fp32 sum, and the decays
+// in P are the exponential of an fp64 difference, so that neither is rounded to
+// the storage type, or to fp32 logarithms, before its product.  A single bf16
+// scan has one rounding more in each (Q~ to bf16, wy_decay's logarithms to fp32)
+// and its output waves one multiplication less per value.
 // The scan reads the keys from the input itself and applies their decay
 // factors in registers: the update takes K^T (diag(e^{g_C - g}) U), so no
 // scaled copy of K is written.
@@ -54,6 +61,7 @@ template <class E> struct Params {
     int G, NG;        // chunks per scan group, number of groups
     float *gf;        // per (b*H + h, chunk): e^{g_C - g_r} [64], g_C (fp64), e^{g_C}, 1 unused
     E *W, *Ut, *Qf, *Pf;
+    float *er;        // RAW: per (b*H + h, chunk): e^{g_r} [64]
     E *Nf;            // per (b*H + h, group): N_g = Phi_g - Gamma_g I, fragment-major
     float *PsiT;      // per (b*H + h, group): Psi_g^T [Dv][Dk]
     double *lgam;     // per (b*H + h, group): log Gamma_g
@@ -106,7 +114,7 @@ __device__ __forceinline__ float wy_decay(const double *sg, const float *sgl, in
 
 constexpr int kWyWaves = 8;
 
-template <class E, int DK, int DV>
+template <class E, int DK, int DV, bool RAW>
 __global__ __launch_bounds__(64 * kWyWaves)
 __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_wy_kernel(Params<E> p) {
     using L = WyLds<E, DK, DV>;
@@ -254,7 +262,8 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
         for (int r = 0; r < 16; ++r) sT[(base + r) * L::LDA + base + j] = x[r];
     } else {
         // Fused output: job (rt, m) writes, for token tile rt,
-        //   Qf[rt][kb][lane][e] = e^{g_r} Q[r][32 kb + 8 lg + e]      (m = 0 jobs)
+        //   Qf[rt][kb][lane][e] = e^{g_r} Q[r][32 kb + 8 lg + e]      (m = 0 jobs; RAW: Q, and
+        //                         er[r] = e^{g_r})
         //   Pf[rt][m][lane][e]  = e^{g_r - g_s} q_r . k_s (s <= r, else 0), s = 32 m + 8 lg + e,
         // the row fragments (B operands over d, resp. s) of the fused output.
         // P^T tiles take their s rows in P32 order, so a tile pair is one
@@ -265,10 +274,12 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
                 E *Qf = p.Qf + cidx * (size_t)kChunk * DK + l * 8;
 #pragma unroll
                 for (int kb = 0; kb < DK / 32; ++kb) {
-                    const f32x4 lo = TR::to_f32(TR::lo(qf[kb])) * er, hi = TR::to_f32(TR::hi(qf[kb])) * er;
-                    TR::store8(Qf + (size_t)(qjob_rt * (DK / 32) + kb) * 512,
-                               TR::cat(TR::from_f32(lo), TR::from_f32(hi)));
+                    frag qs = qf[kb];
+                    if constexpr (!RAW)
+                        qs = TR::cat(TR::from_f32(TR::to_f32(TR::lo(qs)) * er), TR::from_f32(TR::to_f32(TR::hi(qs)) * er));
+                    TR::store8(Qf + (size_t)(qjob_rt * (DK / 32) + kb) * 512, qs);
                 }
+                if (RAW && lg == 0) p.er[cidx * kChunk + rq] = er;
             }
             E *Pf = p.Pf + cidx * (size_t)kChunk * kChunk + l * 8;
             const int m = qjob_m;
@@ -282,7 +293,8 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int s2 = 32 * m + 8 * lg + 4 * a + q;
-                    acc[q] = (s2 <= rq) ? wy_decay<E>(sg, sgl, rq, s2) * acc[q] : 0.f;
+                    const float dec = RAW ? expf((float)(sg[rq] - sg[s2])) : wy_decay<E>(sg, sgl, rq, s2);
+                    acc[q] = (s2 <= rq) ? dec * acc[q] : 0.f;
                 }
                 pq[a] = TR::from_f32(acc);
             }
@@ -546,7 +558,7 @@ __device__ __forceinline__ typename Tr<E>::frag kt_frag(const E *Kr, int row0, i
 
 template <int NOW> constexpr int scan_threads() { return (kScanSplit + NOW + 2) * 64; }
 
-template <class E, int DK, int DV, int PHASE, int CT, int NOW>
+template <class E, int DK, int DV, int PHASE, int CT, int NOW, bool RAW>
 __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Params<E> p) {
     using TR = Tr<E>;
     using frag = typename TR::frag;
@@ -662,7 +674,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
         if (w >= NCW) {
             // ---------------- output waves ----------------
             // Wave o forms, for token tiles rt = o + NOW j of each chunk and every
-            // column tile,  O^T = H_{c-1}^T Q~^T + U^T P^T:
+            // column tile,  O^T = H_{c-1}^T Q~^T + U^T P^T  (RAW: H_{c-1}^T Q^T diag(e^g) + U^T P^T):
             //   A operands: the H_{c-1} and U fragments in LDS (B-operand
             //   layout over d, resp. s, which is also the A layout),
             //   B operands: the Qf / Pf row fragments of the chunk.
@@ -671,6 +683,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
             const int o = w - NCW;
             struct Set {
                 frag q[RO][KB], p[RO][2];
+                float er[RO];                            // RAW: e^{g_r}
             };
             // Operands are requested two chunks ahead, in three register sets
             // used in turn (fp32, with longer steps and larger operands: one
@@ -680,13 +693,16 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
             const unsigned lo16 = 16u * l * (sizeof(frag) / 16);
             const char *qp = (const char *)(p.Qf + ((size_t)bh * p.NC + c_begin) * (size_t)kChunk * DK);
             const char *pp = (const char *)(p.Pf + ((size_t)bh * p.NC + c_begin) * (size_t)kChunk * kChunk);
-            int c_req = c_begin;                         // chunk that qp and pp point at
+            const float *ep = p.er + ((size_t)bh * p.NC + c_begin) * (size_t)kChunk + li;
+            int c_req = c_begin;                         // chunk that qp, pp and ep point at
             auto ld = [&](const char *base, int f) { return TR::load8((const E *)(base + f * (int)sizeof(frag) * 64 + lo16)); };
             auto load_q = [&](Set &st, int kb0, int kb1) {
 #pragma unroll
-                for (int j = 0; j < RO; ++j)
+                for (int j = 0; j < RO; ++j) {
 #pragma unroll
                     for (int kb = kb0; kb < kb1; ++kb) st.q[j][kb] = ld(qp, (o + NOW * j) * KB + kb);
+                    if (RAW && kb0 == 0) st.er[j] = ep[16 * (o + NOW * j)];
+                }
             };
             auto load_p = [&](Set &st) {
 #pragma unroll
@@ -700,6 +716,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
                     ++c_req;
                     qp += (size_t)kChunk * DK * sizeof(E);
                     pp += (size_t)kChunk * kChunk * sizeof(E);
+                    ep += kChunk;
                 }
             };
             const size_t ostride = (size_t)p.H * DV;     // elements from one token's row to the next one's
@@ -725,6 +742,7 @@ __global__ __launch_bounds__(scan_threads<NOW>()) void gdn_chunkscan_kernel(Para
                         acc[j][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int kb = 0; kb < KB; ++kb) acc[j][ct] = TR::mma(hb[ct][kb], st.q[j][kb], acc[j][ct]);
+                        if constexpr (RAW) acc[j][ct] *= st.er[j];
                     }
                 lds_only_barrier();                      // B2(c)
                 frag ub[CT][2];
