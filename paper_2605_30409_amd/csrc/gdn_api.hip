@@ -313,14 +313,25 @@ hipError_t dispatch(const gdn::Params<E> &p, int Dk, int Dv, hipStream_t s, Stag
 // Measured (us a call, one pass -> slabs): T = 12288, H = 16 271 -> 207, T = 16384
 // 388 -> 269, T = 42240, H = 32 1231 -> 1008, 80 heads of D = 64 at T = 10560
 // 358 -> 303.  Slabs of 112 MB: 104 to 128 are equal, 88 and 160 up to 5 and 14 %
-// slower, 40 no gain (each slab's launches and ring fill cost some 8 us).  Below
-// 144 MB in all it makes no difference.  Fewer than 16 chunks to a slab (more
-// than 127 heads) would pay more for the carried state than it saves; the fp32
-// path is bound by its MFMAs and gains nothing.
-constexpr long long kSlabBytes = 112LL << 20, kSlabsFrom = 144LL << 20;
+// slower, 40 no gain (each slab's launches and ring fill cost some 8 us).
+// Two slabs against one pass over the records' size: 16 heads of D = 128 at 119 MB
+// 145.7 -> 151.8, 127 MB 158.3 -> 158.0, 134 MB 171.3 -> 165.2, 140 MB 185.8 ->
+// 172.3, 144.4 MB (T = 10560) 196.1 -> 177.5; 32 heads at 114 MB 98.9 -> 109.3, 128
+// MB 116.9 -> 116.3, 136 MB 132.5 -> 123.0; 64 heads at 126 MB 98.6 -> 103.4, 140 MB
+// 113.6 -> 112.1; 80 heads of D = 64 at 132 MB 100.7 -> 103.1, 142 MB 107.6 -> 106.4;
+// 16 of D = 64 at 124 MB 170.6 -> 177.5, 136 MB 191.0 -> 192.1, 146 MB 218.3 ->
+// 206.2; 16 of 128 x 64 at 121 MB 160.9 -> 164.4, 133 MB 182.3 -> 177.4.  The
+// curves cross between 127 and 138 MB; with the line at 132 MB none of these shapes
+// loses more than some 3 % near it.
+// Fewer than 16 chunks to a slab (more than 128 heads of D = 128, 224 of D = 64)
+// would pay more for the carried state than it saves (200 heads of D = 128, 16
+// chunks 168.3 -> 171.1, 32 chunks 321.8 -> 341.6); the fp32 path is bound by its
+// MFMAs and gains nothing.
+constexpr long long kSlabBytes = 112LL << 20, kSlabsFrom = 132LL << 20;
 
-// Chunks per slab (NC: one pass).  Two slabs or more leave NC / 2 - 1 >= 7 chunks
-// of W records for the carried state, which takes Dv / 32 <= 4.
+// Chunks per slab (NC: one pass).  More than 132 MB with 16 chunks or more to 112 MB
+// are 19 chunks or more, so the first slab leaves NC / 2 >= 9 chunks of W records
+// for the carried state, which takes Dv / 32 <= 4.
 template <class E> int slab_chunks(const gdn::Params<E> &p, int Dk, int Dv) {
     if (sizeof(E) != 2 || p.NG > 1) return p.NC;
     const long long col = 2LL * kChunk * (2 * Dk + Dv + kChunk) * p.B * p.H, most = kSlabBytes / col;

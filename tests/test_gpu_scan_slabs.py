@@ -8,7 +8,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,H,T,Dk,Dv,state", [
-    (1, 32, 5312, 128, 128, True),     # 83 chunks, 152 MB: two slabs of 42 and 41
+    (1, 32, 5312, 128, 128, True),     # 83 chunks, 145 MB: two slabs of 42 and 41
+    (2, 24, 3300, 128, 128, True),     # 52 chunks, 137 MB: just over the size from which there are two
     (1, 32, 5249, 128, 128, False),    # a last chunk of one token, no state in
     (4, 20, 8000, 64, 64, True),       # 125 chunks of 80 narrow heads: three slabs
     (2, 24, 6401, 64, 128, True),
