@@ -183,13 +183,15 @@ int gdn_chunk_forward_ex(const void *q, const void *k, const void *v,
  * back to back between two HIP events recorded on that stream (a stage's
  * launches are identical re-runs, since a stage only reads the inputs and the
  * previous stages' results), then synchronizes the stream and writes the mean
- * duration of one launch of each stage in milliseconds to stage_ms[0..4]
+ * duration of each stage over one call in milliseconds to stage_ms[0..4]
  * (host memory): [0] WY transform, [1] group transfer maps, [2] scan over
  * groups, [3] chunk states and output, [4] always 0 (stage 3 forms the
  * output).  Stages that do not run for this shape (1 and 2 with a single scan
- * group) report 0; long calls are timed in one pass over their chunks.  state_in ==
- * state_out is rejected with GDN_ERR_ALIAS.  The outputs are those of one
- * ordinary call.  Creates and destroys its own events.
+ * group) report 0.  A long call that runs in several slabs of chunks is timed as
+ * it runs, slab after slab with a synchronization behind each, and a stage's
+ * figure is the sum over the slabs.  state_in == state_out is rejected with
+ * GDN_ERR_ALIAS.  The outputs are those of one ordinary call.  Creates and
+ * destroys its own events.
  */
 int gdn_profile_stages(const void *q, const void *k, const void *v,
                        const float *alpha, const float *beta, const float *state_in,

@@ -5,6 +5,7 @@
 #include <cstdint>
 #include <mutex>
 #include <unordered_map>
+#include <utility>
 #include <vector>
 
 #include "gdn.h"
@@ -205,14 +206,27 @@ hipError_t launch(const void *fn, dim3 grid, dim3 block, size_t lds, hipStream_t
     return hipLaunchKernel(fn, grid, block, args, lds, s);
 }
 
-constexpr int kStages = 5;  // WY transform, group transfers, group scan, chunk states with output; none (the output's once)
+constexpr int kStages = 4;  // WY transform, group transfers, group scan, chunk states with output
 
 // Stage timing (measurement aid): every stage that launches is enqueued `reps`
-// times back to back between the events ev[2 s] and ev[2 s + 1].
+// times back to back between the events ev[2 s] and ev[2 s + 1]; collect() waits
+// for them and adds a launch's mean duration to ms[s] (a call in slabs: once each).
 struct StageTiming {
-    int reps;
     hipEvent_t ev[2 * kStages];
     bool ran[kStages];
+    float ms[kStages];
+    int reps;
+    hipError_t collect() {
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < kStages && e == hipSuccess; ++i) {
+            if (!ran[i]) continue;
+            float t = 0.f;
+            e = hipEventSynchronize(ev[2 * i + 1]);
+            if (e == hipSuccess) e = hipEventElapsedTime(&t, ev[2 * i], ev[2 * i + 1]);
+            ms[i] += t / reps;
+        }
+        return e;
+    }
 };
 
 template <class E, int DK, int DV, bool RAW>
@@ -274,7 +288,7 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
     };
     hipError_t er = hipSuccess;
     for (int i = 0; i < kStages && er == hipSuccess; ++i) {
-        const bool runs = (i == 1 || i == 2) ? p.NG > 1 : i != 4;
+        const bool runs = (i == 1 || i == 2) ? p.NG > 1 : true;
         if (tm) tm->ran[i] = runs;
         if (!runs) continue;
         if (!tm) {
@@ -331,7 +345,7 @@ constexpr long long kSlabBytes = 112LL << 20, kSlabsFrom = 132LL << 20;
 
 // Chunks per slab (NC: one pass).  More than 132 MB with 16 chunks or more to 112 MB
 // are 19 chunks or more, so the first slab leaves NC / 2 >= 9 chunks of W records
-// for the carried state, which takes Dv / 32 <= 4.
+// for the carried state, which takes Dv / 32 <= 4, twice.
 template <class E> int slab_chunks(const gdn::Params<E> &p, int Dk, int Dv) {
     if (sizeof(E) != 2 || p.NG > 1) return p.NC;
     const long long col = 2LL * kChunk * (2 * Dk + Dv + kChunk) * p.B * p.H, most = kSlabBytes / col;
@@ -340,20 +354,27 @@ template <class E> int slab_chunks(const gdn::Params<E> &p, int Dk, int Dv) {
     return (int)((p.NC + n - 1) / n);
 }
 
-// The whole call; with stage timing always in one pass.
+// The whole call.  The carried state alternates between two buffers, so a slab
+// whose stages are timed over several launches finds its state as it was.
 template <class E>
 hipError_t run_slabs(const gdn::Params<E> &p, int Dk, int Dv, hipStream_t s, StageTiming *tm) {
     const int SC = slab_chunks(p, Dk, Dv);
-    if (tm || SC >= p.NC) return dispatch(p, Dk, Dv, s, tm);
+    if (SC >= p.NC) {
+        const hipError_t e = dispatch(p, Dk, Dv, s, tm);
+        return tm && e == hipSuccess ? tm->collect() : e;
+    }
     float *carry = (float *)(p.W + (size_t)p.B * p.H * SC * kChunk * Dk);
+    float *other = carry + (size_t)p.B * p.H * Dk * Dv;
     hipError_t e = hipSuccess;
     for (int c0 = 0; c0 < p.NC && e == hipSuccess; c0 += SC) {
         gdn::Params<E> r = p;
         r.c0 = c0;
         r.NC = r.G = p.NC - c0 < SC ? p.NC - c0 : SC;
-        if (c0) r.state_in = carry;
+        if (c0) r.state_in = other;
         if (c0 + SC < p.NC) r.state_out = carry;
         e = dispatch(r, Dk, Dv, s, tm);
+        if (tm && e == hipSuccess) e = tm->collect();
+        std::swap(carry, other);
     }
     return e;
 }
@@ -1045,11 +1066,9 @@ int gdn_profile_stages(const void *q, const void *k, const void *v, const float 
                      is_bf16 != 0, scan_group, ws, ws_bytes, stream, &tm);
     if (status == GDN_OK && hipStreamSynchronize((hipStream_t)stream) != hipSuccess)
         status = GDN_ERR_HIP;
-    for (int i = 0; i < kStages && status == GDN_OK; ++i) {
-        float ms = 0.f;
-        if (tm.ran[i] && hipEventElapsedTime(&ms, tm.ev[2 * i], tm.ev[2 * i + 1]) != hipSuccess)
-            status = GDN_ERR_HIP;
-        stage_ms[i] = tm.ran[i] ? ms / reps : 0.f;
+    if (status == GDN_OK) {
+        for (int i = 0; i < kStages; ++i) stage_ms[i] = tm.ms[i];
+        stage_ms[kStages] = 0.f;                 // once the output's, which stage 3 now forms
     }
     for (auto &e : tm.ev)
         if (e) (void)hipEventDestroy(e);

@@ -222,7 +222,8 @@ STAGE_NAMES = ("wy", "group_transfer", "group_scan", "chunk_states", "output")
 
 def gdn_profile_stages(q, k, v, alpha, beta, state_in, out, state_out, ws, reps=20, chunk=CHUNK,
                        scan_group=0, stream=None):
-    """Mean per-stage durations in ms over `reps` runs, in the order of STAGE_NAMES."""
+    """Mean per-stage durations of one call in ms over `reps` runs, in the order of
+    STAGE_NAMES (the last is always 0; a call in slabs: summed over them)."""
     is_bf16 = q.dtype == torch.bfloat16
     ms = (ctypes.c_float * len(STAGE_NAMES))()
     _call("gdn_profile_stages", q, k, v, alpha, beta, state_in, out, state_out, chunk,
