@@ -134,9 +134,10 @@ size_t gdn_workspace_bytes_ex(int B, int H, int T, int Dk, int Dv, int chunk, in
 /*
  * Host-only consistency check of the workspace layout (no HIP call): for the
  * path a call with these arguments takes, every region of the workspace
- * (per-chunk gate records of key decay factors and chunk decay, -W, U~t, the
- * output's scaled queries and masked scores, and the grouped scan's transfers,
- * offsets, log decays and entry states) starts 256-byte aligned and spans at
+ * (the queries' decay factors, per-chunk gate records of key decay factors and
+ * chunk decay, -W with the states carried between slabs, U~t, the output's
+ * queries and masked scores, and the grouped scan's transfers, offsets, log
+ * decays and entry states) starts 256-byte aligned and spans at
  * least the highest byte the kernels index in it (their index expressions at
  * the largest chunk and group index).  Returns GDN_OK, the 1-based number of
  * the first region that fails, or GDN_ERR_SHAPE / GDN_ERR_UNSUPPORTED.

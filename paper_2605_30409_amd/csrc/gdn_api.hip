@@ -76,6 +76,43 @@ WsLayout ws_layout(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
     return L;
 }
 
+// A single-group call whose chunk records (W, U~, Q~, P: 56 KB a chunk and head at
+// D = 128) outgrow the 256 MB memory-side cache is run in slabs of consecutive
+// chunks that do not: the WY kernel and the scan of one slab, then the next
+// one's in the same records, the state carried in fp32 through the workspace
+// (the records past the first slab are free).  The scan then reads the records
+// from that cache and not from HBM, which takes them in and out at half the
+// speed the scan needs.  Same kernels, same order of every sum: same bits.
+// Measured (us a call, one pass -> slabs): T = 12288, H = 16 271 -> 207, T = 16384
+// 388 -> 269, T = 42240, H = 32 1231 -> 1008, 80 heads of D = 64 at T = 10560
+// 358 -> 303.  Slabs of 112 MB: 104 to 128 are equal, 88 and 160 up to 5 and 14 %
+// slower, 40 no gain (each slab's launches and ring fill cost some 8 us).
+// Two slabs against one pass over the records' size: 16 heads of D = 128 at 119 MB
+// 145.7 -> 151.8, 127 MB 158.3 -> 158.0, 134 MB 171.3 -> 165.2, 140 MB 185.8 ->
+// 172.3, 144.4 MB (T = 10560) 196.1 -> 177.5; 32 heads at 114 MB 98.9 -> 109.3, 128
+// MB 116.9 -> 116.3, 136 MB 132.5 -> 123.0; 64 heads at 126 MB 98.6 -> 103.4, 140 MB
+// 113.6 -> 112.1; 80 heads of D = 64 at 132 MB 100.7 -> 103.1, 142 MB 107.6 -> 106.4;
+// 16 of D = 64 at 124 MB 170.6 -> 177.5, 136 MB 191.0 -> 192.1, 146 MB 218.3 ->
+// 206.2; 16 of 128 x 64 at 121 MB 160.9 -> 164.4, 133 MB 182.3 -> 177.4.  The
+// curves cross between 127 and 138 MB; with the line at 132 MB none of these shapes
+// loses more than some 3 % near it.
+// Fewer than 16 chunks to a slab (more than 128 heads of D = 128, 224 of D = 64)
+// would pay more for the carried state than it saves (200 heads of D = 128, 16
+// chunks 168.3 -> 171.1, 32 chunks 321.8 -> 341.6); the fp32 path is bound by its
+// MFMAs and gains nothing.
+constexpr long long kSlabBytes = 112LL << 20, kSlabsFrom = 132LL << 20;
+
+// Chunks per slab (NC: one pass).  More than 132 MB with 16 chunks or more to 112 MB
+// are 19 chunks or more, so the first slab leaves NC / 2 >= 9 chunks of W records
+// for the carried state, which takes Dv / 32 <= 4, twice.
+int slab_chunks(int B, int H, int NC, int NG, int Dk, int Dv, size_t esz) {
+    if (esz != 2 || NG > 1) return NC;
+    const long long col = 2LL * kChunk * (2 * Dk + Dv + kChunk) * B * H, most = kSlabBytes / col;
+    if (col * NC <= kSlabsFrom || most < 16) return NC;
+    const long long n = (NC + most - 1) / most;
+    return (int)((NC + n - 1) / n);
+}
+
 // Bytes each workspace region must span for the kernels that use it, from the
 // kernels' index expressions evaluated at their largest indices (chunk index
 // cidx = B H NC - 1, group index gidx = B H NG - 1, lane 63, last fragment):
@@ -98,6 +135,12 @@ WsNeeds ws_needs(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
     n.gf = (cmax * kGateRec + kGateRec) * 4;
     // -W fragment ((wv * 4 + st) * 2 + kb) * 512 + l * 8, 8 elements
     n.W = (cmax * kChunk * Dk + ((((size_t)Dk / 64 - 1) * 4 + 3) * 2 + 1) * 512 + 63 * 8 + 8) * esz;
+    // in slabs: the carried states, [B H][Dk][Dv] fp32 twice, behind the first slab's records
+    const size_t SC = slab_chunks(B, H, (int)NC, (int)NG, Dk, Dv, esz);
+    if (SC < NC) {
+        const size_t carry = (size_t)B * H * (SC * kChunk * Dk * esz + 2 * (size_t)Dk * Dv * 4);
+        if (carry > n.W) n.W = carry;
+    }
     // U~t quad (4 jt + st) * 256 + l * 4, 4 elements
     n.Ut = (cmax * Dv * kChunk + (4 * (NJ - 1) + 3) * 256 + 63 * 4 + 4) * esz;
     // WY: Qf (rt * KB + kb) * 512 + l * 8 and Pf (rt * 2 + m) * 512 + l * 8
@@ -317,48 +360,11 @@ hipError_t dispatch(const gdn::Params<E> &p, int Dk, int Dv, hipStream_t s, Stag
     return dispatch_raw<E, true>(p, Dk, Dv, s, tm);
 }
 
-// A single-group call whose chunk records (W, U~, Q~, P: 56 KB a chunk and head at
-// D = 128) outgrow the 256 MB memory-side cache is run in slabs of consecutive
-// chunks that do not: the WY kernel and the scan of one slab, then the next
-// one's in the same records, the state carried in fp32 through the workspace
-// (the records past the first slab are free).  The scan then reads the records
-// from that cache and not from HBM, which takes them in and out at half the
-// speed the scan needs.  Same kernels, same order of every sum: same bits.
-// Measured (us a call, one pass -> slabs): T = 12288, H = 16 271 -> 207, T = 16384
-// 388 -> 269, T = 42240, H = 32 1231 -> 1008, 80 heads of D = 64 at T = 10560
-// 358 -> 303.  Slabs of 112 MB: 104 to 128 are equal, 88 and 160 up to 5 and 14 %
-// slower, 40 no gain (each slab's launches and ring fill cost some 8 us).
-// Two slabs against one pass over the records' size: 16 heads of D = 128 at 119 MB
-// 145.7 -> 151.8, 127 MB 158.3 -> 158.0, 134 MB 171.3 -> 165.2, 140 MB 185.8 ->
-// 172.3, 144.4 MB (T = 10560) 196.1 -> 177.5; 32 heads at 114 MB 98.9 -> 109.3, 128
-// MB 116.9 -> 116.3, 136 MB 132.5 -> 123.0; 64 heads at 126 MB 98.6 -> 103.4, 140 MB
-// 113.6 -> 112.1; 80 heads of D = 64 at 132 MB 100.7 -> 103.1, 142 MB 107.6 -> 106.4;
-// 16 of D = 64 at 124 MB 170.6 -> 177.5, 136 MB 191.0 -> 192.1, 146 MB 218.3 ->
-// 206.2; 16 of 128 x 64 at 121 MB 160.9 -> 164.4, 133 MB 182.3 -> 177.4.  The
-// curves cross between 127 and 138 MB; with the line at 132 MB none of these shapes
-// loses more than some 3 % near it.
-// Fewer than 16 chunks to a slab (more than 128 heads of D = 128, 224 of D = 64)
-// would pay more for the carried state than it saves (200 heads of D = 128, 16
-// chunks 168.3 -> 171.1, 32 chunks 321.8 -> 341.6); the fp32 path is bound by its
-// MFMAs and gains nothing.
-constexpr long long kSlabBytes = 112LL << 20, kSlabsFrom = 132LL << 20;
-
-// Chunks per slab (NC: one pass).  More than 132 MB with 16 chunks or more to 112 MB
-// are 19 chunks or more, so the first slab leaves NC / 2 >= 9 chunks of W records
-// for the carried state, which takes Dv / 32 <= 4, twice.
-template <class E> int slab_chunks(const gdn::Params<E> &p, int Dk, int Dv) {
-    if (sizeof(E) != 2 || p.NG > 1) return p.NC;
-    const long long col = 2LL * kChunk * (2 * Dk + Dv + kChunk) * p.B * p.H, most = kSlabBytes / col;
-    if (col * p.NC <= kSlabsFrom || most < 16) return p.NC;
-    const long long n = (p.NC + most - 1) / most;
-    return (int)((p.NC + n - 1) / n);
-}
-
 // The whole call.  The carried state alternates between two buffers, so a slab
 // whose stages are timed over several launches finds its state as it was.
 template <class E>
 hipError_t run_slabs(const gdn::Params<E> &p, int Dk, int Dv, hipStream_t s, StageTiming *tm) {
-    const int SC = slab_chunks(p, Dk, Dv);
+    const int SC = slab_chunks(p.B, p.H, p.NC, p.NG, Dk, Dv, sizeof(E));
     if (SC >= p.NC) {
         const hipError_t e = dispatch(p, Dk, Dv, s, tm);
         return tm && e == hipSuccess ? tm->collect() : e;

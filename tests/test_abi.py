@@ -146,6 +146,18 @@ def test_workspace_regions_cover_kernel_indexing(is_bf16, Dk, Dv):
     assert L.gdn_workspace_check(1, 1, 64, 96, 64, 64, 1, 0) == -3
 
 
+@pytest.mark.parametrize("Dk,Dv", [(64, 64), (128, 128), (64, 128), (128, 64)])
+def test_workspace_holds_the_states_carried_between_slabs(Dk, Dv):
+    """Head counts up to the last that run in slabs, from the first chunk count that
+    does (132 MB of records): the W records behind the first slab span two states."""
+    L = gdn.lib()
+    for heads in list(range(1, 226, 7)) + [127, 128, 224]:
+        per_chunk = 128 * (2 * Dk + Dv + 64) * heads
+        first = (132 << 20) // per_chunk
+        for nc in (first, first + 1, first + 2, first + 3, 2 * first, 5 * first + 1):
+            assert L.gdn_workspace_check(1, heads, 64 * nc, Dk, Dv, 64, 1, 64 * nc) == 0, (heads, nc)
+
+
 def test_noalloc_rejects_workspace_beyond_its_array():
     """The allocation-free call returns GDN_ERR_WORKSPACE, before any HIP call,
     when the shape's workspace exceeds its static array (64 MiB): one 1280x704
