@@ -68,8 +68,6 @@ template <> struct Tr<uint16_t> {
         return frag{lo[0], lo[1], hi[0], hi[1]};
     }
     static __device__ __forceinline__ quad lo(frag f) { return quad{f[0], f[1]}; }
-    // all bits kept (m = ~0) or the quad zeroed (m = 0)
-    static __device__ __forceinline__ quad mask(quad v, uint32_t m) { return quad{v[0] & m, v[1] & m}; }
     static __device__ __forceinline__ quad hi(frag f) { return quad{f[2], f[3]}; }
     static __device__ __forceinline__ f32x4 mma(frag a, frag b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
@@ -95,10 +93,6 @@ template <> struct Tr<float> {
         return frag{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     }
     static __device__ __forceinline__ quad lo(frag f) { return quad{f[0], f[1], f[2], f[3]}; }
-    static __device__ __forceinline__ quad mask(quad v, uint32_t m) {
-        return quad{__uint_as_float(__float_as_uint(v[0]) & m), __uint_as_float(__float_as_uint(v[1]) & m),
-                    __uint_as_float(__float_as_uint(v[2]) & m), __uint_as_float(__float_as_uint(v[3]) & m)};
-    }
     static __device__ __forceinline__ quad hi(frag f) { return quad{f[4], f[5], f[6], f[7]}; }
     static __device__ __forceinline__ f32x4 mma(frag a, frag b, f32x4 c) {
 #pragma unroll

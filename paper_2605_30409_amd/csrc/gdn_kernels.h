@@ -503,23 +503,12 @@ template <class E, int DK, int CT, int NOW> struct ScanLds {
     static constexpr int DL = (CAP - HX - UX * (NOW ? 2 : 1)) / SLOT;
     // the loaders wait with DEPTH - 1 younger chunks in flight: vmcnt <= 63
     static constexpr int DVM = 1 + 63 / (NC_W / 2 + 1);
-    static constexpr int D0 = DL < DVM ? DL : DVM;
-    static constexpr int DEPTH = D0 < 4 ? 2 : 4;           // divides the compute waves' unroll of four
+    static constexpr int DEPTH = 4;                        // the compute waves' unroll of four
     static constexpr int oH = DEPTH * SLOT, oU = oH + HX, oUo = oU + UX;
     static constexpr size_t bytes = oUo + (NOW ? UX : 0);
-    static_assert(D0 >= 2, "scan ring needs two slots");
+    static_assert(DEPTH <= DL && DEPTH <= DVM, "the ring fits the LDS and its waits the counter");
     static_assert(W_BYTES % 1024 == 0 && SLOT % 16 == 0, "whole 1 KB copies, aligned slots");
 };
-
-// Copy N whole KB from global to LDS: instruction i moves bytes
-// [1024 i, 1024 i + 1024), lane l its 16 bytes at 1024 i + 16 l.
-template <int N> __device__ __forceinline__ void copy_kb(const void *src, void *dst, int l) {
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-        __builtin_amdgcn_global_load_lds((const void *)((const char *)src + 1024 * i + 16 * l),
-                                         (__attribute__((address_space(3))) void *)((char *)dst + 1024 * i),
-                                         16, 0, 0);
-}
 
 // Key rows in the scan's LDS ring: row r (a token of the chunk) holds its DK
 // elements with the 16-byte granules permuted, granule g stored at g ^ kswz(r).
