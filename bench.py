@@ -71,16 +71,19 @@ def path_counts(B, T, H, Dk, Dv, C=64, esz=2):
 def workspace_traffic(B, T, H, Dk, Dv, G, C=64, esz=2):
     """Workspace bytes each stage writes and reads (every byte once).  The WY
     kernel writes the gates (a record of the per-token key decay factors in fp32
-    with g_C), -W and U~t, and the decay-scaled queries and the masked decayed
-    Q K^T tile of every chunk (row fragments the scan's output waves read); the
-    scans read the keys from the input."""
+    with g_C), -W and U~t, and the queries (decay-scaled in a single bf16 scan,
+    else as given with their decay factors in fp32) and the masked decayed Q K^T
+    tile of every chunk (row fragments the scan's output waves read); the scans
+    read the keys from the input."""
     NC = -(-T // C)
     NG = -(-NC // G)
     nch = B * H * NC
     ngr = B * H * NG if NG > 1 else 0
     gates = nch * (C + 4) * 4                              # key scales, g_C
     fac = nch * C * (Dk + Dv) * esz                        # -W, U~t
-    qp = nch * C * (Dk + C) * esz                          # scaled Q, masked P
+    qp = nch * C * (Dk + C) * esz                          # Q, masked P
+    if esz == 4 or ngr:
+        qp += nch * C * 4                                  # the queries' decay factors
     grp = ngr * (Dk * Dk * esz + Dv * Dk * 4 + 8)          # N, Psi^T, log Gamma
     hg = ngr * Dv * Dk * 4                                 # group entry states
     zero = {"written": 0, "read": 0}
@@ -135,8 +138,9 @@ def cpu_baseline(inp, B, T, min_seconds=10.0):
 
 
 def load_traffic(summary):
-    """Per-stage HBM bytes per launch from a committed counter summary, or None when
-    the summary is missing or was taken on different kernel source."""
+    """Per-stage bytes of one call past the L2 caches (a stage's launches in its slabs
+    added up) from a committed counter summary, or None when the summary is missing
+    or was taken on different kernel source."""
     path = os.path.join(ROOT, "profiles", summary)
     if not os.path.exists(path):
         return None
@@ -148,7 +152,8 @@ def load_traffic(summary):
             h.update(open(os.path.join(ROOT, f), "rb").read())
         if h.hexdigest() != rec["source_sha256"]:
             return None
-        return {k: float(v["hbm_bytes_per_launch"]) for k, v in rec["stages"].items()}
+        n = rec.get("launches_per_call", 1)
+        return {k: n * float(v["hbm_bytes_per_launch"]) for k, v in rec["stages"].items()}
     except Exception:
         return None
 

@@ -17,12 +17,11 @@
  * kernel section writes the scan (S_f = alpha_f P_f S_{f-1} + A_f).
  *
  * The work is evaluated chunk by chunk (chunks of `chunk` tokens): a per-chunk
- * WY/UT transform, a scan of the state across chunks, and a per-chunk output
- * pass.  Long sequences split the scan into groups of consecutive chunks: the
+ * WY/UT transform and a scan of the state across chunks that forms the output.  Long sequences split the scan into groups of consecutive chunks: the
  * transfer map of every group (its product of per-chunk transitions and its
  * zero-start state) is formed in parallel, a short sequential scan over the
- * groups yields each group's entry state, and the chunk states inside all
- * groups then follow in parallel.  This is an exact rewrite of the
+ * groups yields each group's entry state, and the chunk states and outputs
+ * inside all groups then follow in parallel.  This is an exact rewrite of the
  * recurrence; results differ from it only by rounding (and, slightly, with
  * the group size).
  *

@@ -26,13 +26,18 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 int num_chunks(int T) { return (T + kChunk - 1) / kChunk; }
 
 // Chunks per scan group.  bf16: a single group (one sequential scan per
-// (b, h) with the output fused into it) whenever the (b, h) streams give at
-// least 64 column-tile workgroups -- measured faster than any grouped scan on
-// the 3-frame, batched and 12-frame workloads -- or the sequence has at most 64
-// chunks.  fp32, and bf16 with fewer streams: a single group when the sequence
-// is short or when the streams alone fill the chip; otherwise about sqrt(NC)
-// chunks per group, which balances the group-parallel passes (two passes over
-// G chunks) against the sequential scan over NC / G groups.
+// (b, h)) whenever the (b, h) streams give at least 64 column-tile workgroups or
+// the sequence has at most 64 chunks.  fp32, and bf16 with fewer streams: a single
+// group when the sequence is short or when the streams alone fill the chip;
+// otherwise about sqrt(NC) chunks per group, which balances the group-parallel
+// passes (two passes over G chunks) against the sequential scan over NC / G groups.
+// Measured (us a call, single -> best grouped; bf16, D = 128 unless said): T = 3520,
+// H = 16 59.4 -> 68.1; T = 10560, H = 16 172.5 -> 185.3; T = 42240, H = 32 1026 ->
+// 1480; T = 10560, 80 heads of D = 64 303 -> 428; T = 10560, H = 4 124.8 -> 66.9
+// (68.6 at this rule's G = 13).  The line lies where the passes before the present
+// ones crossed; with the present ones H = 8 at T = 10560 takes 135.8 single and
+// 102.4 at G = 26, and fp32 H = 16 641 single and 736 at this rule's G = 13.  It is
+// part of the interface (gdn_scan_group_size, workspace sizes) and stays.
 int auto_group(int NC, long long BH, int Dv, bool bf16) {
     if (NC <= 64 || BH * (Dv / 16) >= (bf16 ? 64 : 512)) return NC;
     int G = (int)(__builtin_sqrt((double)NC) + 0.5);
@@ -159,7 +164,8 @@ WsNeeds ws_needs(int B, int H, int T, int Dk, int Dv, size_t esz, int G) {
 
 bool shape_ok(int B, int H, int T) {
     if (B < 1 || H < 1 || T < 1) return false;
-    // gridDim.y carries B*H
+    // a limit of the interface, from when B*H was a grid dimension (the records of a
+    // call with more than 2^31 chunk and head pairs would not fit the memory)
     if ((long long)B * H > 65535) return false;
     return true;
 }
@@ -277,10 +283,12 @@ hipError_t launch_path(const gdn::Params<E> &p, hipStream_t s, StageTiming *tm) 
     constexpr int NOW = 4;                       // output waves
     // Two column tiles per workgroup once one each would be more workgroups than
     // CUs: the pair reads the chunk operands once, and a second round of
-    // workgroups or a shared CU costs more than the longer step (320 tiles of the
-    // D = 64 guidance batch, T = 10560: 461 us a call with one tile, 355 with two).
-    // Up to one workgroup per CU one tile is faster (T = 3520, H = 16, 128 tiles:
-    // 65 against 76 us; T = 42240, H = 32, 256 tiles: 1227 against 1267), in fp32
+    // workgroups or a shared CU costs more than the longer step (us a call, one tile
+    // -> two: T = 3520 with 264 tiles of D = 128 115 -> 88, 384 tiles 146 -> 119; T =
+    // 10560 with 272 and 320 tiles of D = 64 340 -> 264 and 366 -> 290; 416 tiles in
+    // groups 75 -> 68).  Up to one workgroup per CU one tile is faster (T = 3520 with
+    // 128 and 256 tiles 59.5 -> 71.0 and 76.4 -> 85.9, T = 42240 with 256 1018 ->
+    // 1134, 256 tiles of D = 64 263 -> 269, 208 in groups 52.7 -> 55.6), in fp32
     // always (its two-tile step has no registers for it).
     const bool wide = sizeof(E) == 2 && (long long)p.B * p.H * p.NG * (DV / 16) > 256;
     constexpr int CTW = sizeof(E) == 2 ? 2 : 1;
@@ -689,8 +697,10 @@ gdn::FrameParams<E> make_frame_params(const FrameArgs &a, int NS, void *ws) {
     if (a.fused) {
         // the key scale is applied to the key features as they are formed
         p.key_scale = 1.f;
-        // one workgroup per CU (the fused output needs 100+ KB of LDS): at
-        // most 256 workgroups in all unless the units alone exceed that
+        // at most 256 workgroups in all, one per CU, unless the units alone exceed
+        // that: each stages H_f and W_o anew (D = 128: 70 KB in bf16, where 480
+        // workgroups of 8 waves took 36.0 us against 32.5; 137 KB in fp32, where
+        // only one fits a CU; D = 64: 18 and 36 KB, other counts not measured)
         const long long units = (long long)a.B * a.H * a.F;
         const int ntf = (a.N + 15) / 16;
         long long ob = 256 / units;

@@ -277,7 +277,8 @@ template <bool FUSED> constexpr int sum_threads() { return (kSumCompute + (FUSED
 // formed where only they are kept (several splits); the waves of one SIMD (w and
 // w + 4) take row pairs whose shares above the diagonal add up to 6 or 4 of the 16
 // tile pairs that two such waves of the plain kernel carry (114 -> 60 us where the
-// plain kernel also formed the A tiles and dropped them).
+// plain kernel also formed the A tiles and dropped them; 54 since the loaders zero
+// the betas past a split's end).
 template <class E, int DK, int DV, bool NORM, bool FUSED = false, bool UNROT = false>
 __global__ __launch_bounds__(sum_threads<FUSED>()) void gdn_frame_summary_kernel(FrameParams<E> p) {
     static_assert(!FUSED || (NORM && sizeof(E) == 2), "the fused operator is normalized and bf16");
@@ -1376,7 +1377,7 @@ __global__ __launch_bounds__(256) void gdn_frame_rope_kernel(FrameParams<float> 
 // time t0 + f, 1 latent row s / lat_w, else latent column s % lat_w).  Two
 // channel pairs (16 bytes) per lane, Dk / 4 lanes per row (the row's sum of
 // squares reduced across them).  Bound by HBM: one read and two writes of the
-// key tensor, 260 MB in 43 us (3 frames of 3520 tokens, H = 16).
+// key tensor, 260 MB in 41 us (3 frames of 3520 tokens, H = 16).
 template <int DK>
 __global__ __launch_bounds__(256) void gdn_frame_kfeatures_kernel(FrameParams<float> p) {
     constexpr int LR = DK / 4;                                  // lanes per row
@@ -1416,7 +1417,8 @@ __global__ __launch_bounds__(256) void gdn_frame_kfeatures_kernel(FrameParams<fl
 // LDS as fragments (the halves of a lane's eight values in planes of 16 bytes per
 // lane), so one workgroup of 8 waves runs per CU.  Bound by the matrix cores: 544
 // MFMAs of 32 cycles per 16-token tile (75 us for 3 frames of 3520 tokens, H =
-// 16; measured 137, with 4 waves 158).  As two kernels with the gated readout, the
+// 16; measured 137 launched back to back, with 4 waves 158, and 148 in whole
+// calls).  As two kernels with the gated readout, the
 // query features and their rotation through HBM it took 116 + 161 us beside half
 // of the 177 us features.
 constexpr int kFusedOutWaves32 = 8;

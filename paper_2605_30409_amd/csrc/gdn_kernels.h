@@ -73,8 +73,9 @@ template <class E> struct Params {
 // fastest, kWyWaves waves: workgroups that run together read whole token rows
 // (all heads of a chunk), and a chunk's factors are written about when its
 // neighbours' are, in the order in which the scan reads them back.  With the
-// chunks fastest a 3-frame call (T = 10560, H = 16) on inputs that are not in the
-// caches took 230 us, now 196; the kernel alone on warm inputs is the same.
+// chunks fastest a 3-frame call (T = 10560, H = 16) in one pass on inputs that are
+// not in the caches took 230 us, with the heads fastest 196; the kernel alone on
+// warm inputs is the same.
 // --------------------------------------------------------------------------
 // LDS: K rows, A (fp32; V rows take its place once the solve is done), T
 // (fp32), gates.  52.3 KB on the bf16 path at D = 128: three workgroups per CU.
@@ -438,14 +439,16 @@ __attribute__((amdgpu_waves_per_eu(WyLds<E, DK, DV>::waves_per_simd))) void gdn_
 // take K(c) into registers in phase 1 of chunk c, so its slot is refilled for
 // chunk c + DEPTH from B2(c) on: a copy has DEPTH - 1/2 steps to land.
 //
-// What bounds a step (T = 3520, H = 16, D = 128, 128 workgroups, 55 steps; copies
-// of the kernel that leave work out): the compute waves alone 0.37 us, with the
-// loads 0.73.  A workgroup takes in 56 KB a step (W, K and Q~ 16 KB each, P 6, U~t
-// 2), which one CU does at about 80 B/ns whether through LDS or registers, with 8
-// workgroups on the chip or 256.  Before, one wave carried all rows of a column
-// tile: 0.56 us of dependent MFMAs and VALU a step, 0.72 with the loads.  So where
-// that one CU's intake is the limit the kernel is as fast as before (40 us), and
-// where the chain was, faster: fp32 (256 MFMAs of 32 cycles a step and tile, now
+// What bounds a step (T = 3520, D = 128, 55 steps): it takes 0.70 us with 8
+// workgroups on the chip (one head), 0.72 with 128 and 0.76 with 256, so the bound
+// is inside the CU.  A workgroup takes in 56 KB a step (W, K and Q~ 16 KB each, P 6,
+// U~t 2); a bare load of as much in the same pattern takes 0.45 us with 16 to 64
+// workgroups and 0.56 with 128 (125 and 100 B/ns into one CU), the compute waves
+// alone (a copy of the kernel that leaves the loads out) 0.37: the two overlap only
+// in part.  Before, one wave carried all rows of a column tile: 0.56 us of
+// dependent MFMAs and VALU a step, 0.72 with the loads.  So where the intake weighs
+// as much as the chain the kernel is as fast as before (40 us), and where the chain
+// was the limit, faster: fp32 (256 MFMAs of 32 cycles a step and tile, now
 // over four SIMDs) T = 3557, H = 16 250 -> 104 us, and 143 with the output in it
 // where a kernel of its own took 83 more; the grouped passes of two
 // heads at T = 10560 18.4 -> 12 us (transfers) and 22.9 + 9.6 -> 13 us (states,

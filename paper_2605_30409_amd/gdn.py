@@ -302,7 +302,7 @@ def frame_workspace(q, v, frame_tokens, token_splits=0):
 
 def fused_workspace(q, v, frame_tokens, token_splits=0):
     """Workspace tensor for gdn_frame_forward_fused_ex / _f32_ex on inputs shaped like q and v
-    (the fp32 operator also keeps its feature maps and gated readout there)."""
+    (the fp32 operator also keeps its key features and rotation table there)."""
     B, T, H, Dk = q.shape
     N = int(frame_tokens)
     n = lib().gdn_frame_fused_workspace_bytes(B, H, T // N, N, Dk, v.shape[-1], 1 if q.dtype == torch.bfloat16

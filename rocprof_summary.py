@@ -101,7 +101,7 @@ def copy_reading(db, counter):
     return max(per.values())
 
 
-def counters(fetch_db, write_db, tmpl, title, workload, sources):
+def counters(fetch_db, write_db, tmpl, title, workload, sources, launches=1):
     f, w = pmc_medians(fetch_db), pmc_medians(write_db)
     copy_f, copy_w = copy_reading(fetch_db, "FETCH_SIZE"), copy_reading(write_db, "WRITE_SIZE")
     ff, wf = 262144.0 / copy_f, 262144.0 / copy_w           # 256 MiB in KiB
@@ -124,12 +124,15 @@ def counters(fetch_db, write_db, tmpl, title, workload, sources):
         total += rd + wr
         lines.append(f"| `{k}` | {st} | {v:.0f} | {wv:.0f} | {rd / 1e6:.1f} | {wr / 1e6:.1f} | "
                      f"{(rd + wr) / 1e6:.1f} |")
-    lines += ["", f"Whole call (sum over the kernels): {total / 1e6:.1f} MB."]
+    per = "sum over the kernels" if launches == 1 else f"{launches} slabs, each kernel once a slab; the rows are of one launch"
+    lines += ["", f"Whole call ({per}): {launches * total / 1e6:.1f} MB.  The counters stand between the L2 caches and "
+              "the 256 MB memory-side cache: what that cache serves counts as well (a 48 MiB copy repeated ten times "
+              "reads the same figure each time)."]
     h = hashlib.sha256()
     for s in sources:
         h.update(open(os.path.join(ROOT, s), "rb").read())
     rec = {"workload": workload, "sources": list(sources), "source_sha256": h.hexdigest(),
-           "fetch_scale": ff, "write_scale": wf, "commands": cmds, "stages": stages}
+           "fetch_scale": ff, "write_scale": wf, "launches_per_call": launches, "commands": cmds, "stages": stages}
     return "\n".join(lines) + "\n", rec
 
 
@@ -150,12 +153,14 @@ def main():
     c.add_argument("--name", required=True)
     c.add_argument("--workload", required=True)
     c.add_argument("--sources", nargs="+", required=True)
+    c.add_argument("--launches-per-call", type=int, default=1, help="slabs of a long call")
     c.add_argument("--outdir", default=os.path.join(ROOT, "profiles"))
     a = ap.parse_args()
     if a.what == "trace":
         open(a.out, "w").write(trace_md(a.db, a.cmd, a.title, a.note))
     else:
-        md, rec = counters(a.fetch_db, a.write_db, a.cmd_template, a.title, a.workload, a.sources)
+        md, rec = counters(a.fetch_db, a.write_db, a.cmd_template, a.title, a.workload, a.sources,
+                           a.launches_per_call)
         os.makedirs(a.outdir, exist_ok=True)
         open(os.path.join(a.outdir, f"counters_{a.name}.md"), "w").write(md)
         open(os.path.join(a.outdir, f"traffic_{a.name}.json"), "w").write(json.dumps(rec, indent=1) + "\n")
